@@ -86,6 +86,22 @@ def test_block_mass_matches_oracle(dtype, S, B, H):
     np.testing.assert_allclose(M.sum(axis=-1), 1.0, atol=1e-4)
 
 
+@pytest.mark.parametrize("S", [1, 64, 65, 255, 257, 1024, 1025, 1088, 2047])
+@pytest.mark.parametrize("kv_block", [64, 128])
+def test_block_mass_at_the_edges_of_its_groups(S, kv_block):
+    """The kernel takes four q-blocks per workgroup, sums four kv blocks at a
+    time and writes sixteen together: lengths that end inside, at and just past
+    each of them, against the float64 oracle (same bound as above)."""
+    q, k = positional(1, S, 2, torch.bfloat16, S)
+    sm = 1.0 / math.sqrt(128)
+    qd, kd = q.cuda(), k.cuda()
+    _, lse = ops.block_sparse_attn_fwd(qd, kd, kd, None, sm_scale=sm, return_lse=True)
+    out = torch.full((1, 2, (S + 63) // 64, (S + kv_block - 1) // kv_block), float("nan"), device="cuda")
+    M = ops.attn_block_mass(qd, kd, lse, sm_scale=sm, out=out, kv_block=kv_block).cpu().numpy().astype(np.float64)
+    ref = ms.block_mass_all(np64(q), np64(k), sm, kv_block=kv_block)
+    assert np.all(np.abs(M - ref) <= MASS_ATOL + MASS_RTOL * ref), float(np.max(np.abs(M - ref)))
+
+
 def oracle_mask_of(M, top_p, mk, mask_batch):
     """OracleMask whose 'scores' are log-masses: softmax(log m) = m / sum(m),
     so the comparator's near-tie and boundary rules apply to the mass shares."""
