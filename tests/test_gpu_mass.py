@@ -208,6 +208,25 @@ def test_coverage_matches_oracle():
     assert (ops.mask_coverage(own, Md, S).cpu().numpy() >= 0.8 - 1e-6).all()
 
 
+@pytest.mark.parametrize("S,kv_block,p_keep", [(64 * 65 + 1, 64, 0.9), (64 * 130 - 3, 128, 0.6), (100, 64, 1.0)])
+def test_coverage_at_the_edges_of_its_rows(S, kv_block, p_keep):
+    """64 rows at a time, 64 ids of a row at a time: more rows than one round,
+    rows longer than one round, empty rows, ids outside [0, n_kv) skipped; sums
+    in float64 against the oracle."""
+    B, H = 2, 2
+    n, nk = (S + 63) // 64, (S + kv_block - 1) // kv_block
+    g = np.random.Generator(np.random.PCG64(S))
+    M = g.random((B, H, n, nk)).astype(np.float32)
+    rp, ci = wk.random_csr(g, H * n, nk, p_keep, empty_frac=0.1)
+    ref = ms.coverage(rp, ci, 1, M.astype(np.float64), S)
+    rows = [np.concatenate([[-1], ci[rp[r]:rp[r + 1]], [nk]]) for r in range(H * n)]
+    rp2 = np.concatenate([[0], np.cumsum([len(x) for x in rows])])
+    for a, b in ((rp, ci), (rp2, np.concatenate(rows))):
+        mask = ops.BlockMask.from_host(a, b, 1, H, n, block=kv_block)
+        got = ops.mask_coverage(mask, torch.from_numpy(M).cuda(), S).cpu().numpy()
+        np.testing.assert_allclose(got, ref, rtol=1e-13 * nk)
+
+
 def test_full_size_reuse_workload_sampled_rows():
     """Historical request of the 480p reuse workload at full size: sampled
     rows of the GPU block mass against rows the oracle computes one by one
