@@ -131,6 +131,13 @@ __device__ inline void dma16(uint32_t lds, const void* sbase, uint32_t voff) {
 // Wait until at most n vector-memory loads of this wave are outstanding.
 #define CHORUS_WAIT_VMCNT(n) asm volatile("s_waitcnt vmcnt(" #n ")" ::: "memory")
 
+// Before a barrier after which tiles are refilled and LDS data of other waves
+// is read: this wave's direct loads have landed, its LDS reads have returned
+// and its LDS writes are done.  The LDS part is spelled out because the wait
+// that __syncthreads() implies was missing where the barrier opens a loop and
+// the LDS access closes it.
+#define CHORUS_WAIT_LDS_TILES() asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory")
+
 // Walk of the merged kv lists of the two q-blocks (2p, 2p + 1) of a pair,
 // skipping ids outside [0, n).  Each list is walked from its rotated start
 // (walk_target of q-block 2p, the same target for both; 0 for dense

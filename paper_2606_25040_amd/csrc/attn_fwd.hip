@@ -24,11 +24,11 @@
 // global addresses instead of the LDS ones) so that the b128 K reads and the
 // transposed b64 V reads are bank-conflict free.
 // Epilogue: O = O^T / l written as 16-bit, lse = ln(sum exp) in fp32.
-// Template flags: DENSE walks every kv block (no mask); KSCALE multiplies the
-// logits of keys below n_first by beta (first-frame key enhancement, Eq. 1);
-// KV2 reads a mask of 128-token kv blocks and walks each as its two 64-token
-// halves.  Each flag is its own instantiation, so the plain path carries none
-// of the others' work.
+// Template flags: KSCALE multiplies the logits of keys below n_first by beta
+// (first-frame key enhancement, Eq. 1); KV2 reads a mask of 128-token kv blocks
+// and walks each as its two 64-token halves.  Each flag is its own
+// instantiation, so the plain path carries none of the others' work.
+// Without a mask attn_dense_16_kernel below runs instead.
 #include "attn_common.h"
 
 namespace chorus {
@@ -116,7 +116,7 @@ struct TileLoader {
   }
 };
 
-template <bool BF16, bool DENSE, bool KSCALE, bool KV2>
+template <bool BF16, bool KSCALE, bool KV2>
 __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2)))
 void attn_fwd_16_kernel(AttnArgs a) {
   using E = Elt<BF16>;
@@ -131,25 +131,20 @@ void attn_fwd_16_kernel(AttnArgs a) {
   const int i = item % n;
   const int bh = item / n;
   const int h = bh % H, b = bh / H;
-  // DENSE: every kv block (no mask); otherwise the CSR row of (b, h, i).
-  // KV2: the row lists kv blocks of 128 tokens; the walk visits both 64-token
-  // halves of each (positions 2 p and 2 p + 1 of the doubled list).
-  int kb0 = 0, kb1 = n;
-  if (!DENSE) {
-    const int64_t mrow = ((int64_t)(a.mask_batch > 1 ? b : 0) * H + h) * n + i;
-    kb0 = a.row_ptr[mrow];
-    kb1 = a.row_ptr[mrow + 1];
-    if (KV2) {
-      kb0 *= 2;
-      kb1 *= 2;
-    }
+  // The CSR row of (b, h, i).  KV2: it lists kv blocks of 128 tokens and the
+  // walk visits both 64-token halves of each (positions 2 p and 2 p + 1 of the
+  // doubled list).
+  const int64_t mrow = ((int64_t)(a.mask_batch > 1 ? b : 0) * H + h) * n + i;
+  int kb0 = a.row_ptr[mrow], kb1 = a.row_ptr[mrow + 1];
+  if (KV2) {
+    kb0 *= 2;
+    kb1 *= 2;
   }
   ConstI32* cidx = as_constant(a.col_idx);   // scalar loads
-  auto kv_at = [&](int p) { return DENSE ? p : KV2 ? 2 * cidx[p >> 1] + (p & 1) : cidx[p]; };
-  // walk step v visits list position kb0 + (v + rot) mod L (see walk_target);
-  // without a mask every q-block lists every block and starts at block 0
+  auto kv_at = [&](int p) { return KV2 ? 2 * cidx[p >> 1] + (p & 1) : cidx[p]; };
+  // walk step v visits list position kb0 + (v + rot) mod L (see walk_target)
   const int L = kb1 - kb0;
-  const int rot = DENSE ? 0 : walk_rotation(kb0, kb1, walk_target(i, n), kv_at);
+  const int rot = walk_rotation(kb0, kb1, walk_target(i, n), kv_at);
   auto kv_block = [&](int v) {
     const int p = v + rot;
     return kv_at(kb0 + (p >= L ? p - L : p));
@@ -344,34 +339,312 @@ void attn_fwd_16_kernel(AttnArgs a) {
   }
 }
 
+// This wave's share (1 of NW) of a 64 x 128 16-bit tile.
+template <int NW>
+struct SharedTileLoader {
+  static constexpr int kInstr = 16 / NW;   // 1 KB instructions per wave, 4 rows each
+  const char* base;
+  uint32_t ss;
+  uint32_t off;        // lane offset (row r0, swizzled chunk): 4 NW rows on, the swizzle repeats
+  int r0, p;
+  template <bool IS_K>
+  __device__ void init(const uint16_t* b, int64_t stride, int wave, int lane) {
+    base = reinterpret_cast<const char*>(b);
+    ss = (uint32_t)(stride * 2);
+    r0 = 4 * wave + (lane >> 4);
+    p = lane & 15;
+    static_assert(4 * NW % 16 == 0, "the K swizzle has a period of 16 rows");
+    off = (uint32_t)r0 * ss + (uint32_t)(IS_K ? k_swz(r0, p) : v_swz(r0, p)) * 16;
+  }
+  template <bool IS_K>
+  __device__ void load(uint32_t lds, int j, int S, int wave) const {
+    if (j * kBlock + kBlock <= S) {
+      const char* rowj = base + (int64_t)j * kBlock * ss;
+#pragma unroll
+      for (int u = 0; u < kInstr; ++u)
+        dma16(lds + (NW * u + wave) * 1024, rowj + (int64_t)(4 * NW * u) * ss, off);
+    } else {
+#pragma unroll
+      for (int u = 0; u < kInstr; ++u) {
+        const int r = 4 * NW * u + r0;
+        const int c = IS_K ? k_swz(r, p) : v_swz(r, p);
+        const int tok = min(j * kBlock + r, S - 1);
+        dma16(lds + (NW * u + wave) * 1024, base, (uint32_t)tok * ss + (uint32_t)c * 16);
+      }
+    }
+  }
+};
+
+// Dense attention (no mask): every q-block visits every kv block, so NW waves
+// of 32 queries share each tile and the work inside a wave is pipelined.  At
+// step j a wave issues QK^T of block j + 1 (its 16 MFMAs need nothing of block
+// j) beside the exponentials of block j, then PV of block j beside the row max
+// of block j + 1, so the matrix cores have work during the softmax; K and V
+// are double-buffered (64 KB), refilled a whole step ahead, one barrier per kv
+// block.  Each output row takes the same operations in the same order as in
+// the masked kernel: an explicit full mask gives the same bits.
+// Measured at 480p 14B (S = 32,760, 40 heads, bf16): 17.8-18.6 ms, 1,180-1,230
+// TFLOP/s, matrix cores busy 64 % of the cycles, against 22.8-23.2 ms for the
+// masked kernel's two-wave workgroup (46 %); four waves 19.0 ms.  What is left
+// is the clock (1.8 GHz under this load) and the issue of the softmax's vector
+// instructions.
+template <bool BF16, bool KSCALE, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void attn_dense_16_kernel(AttnArgs a, int np) {
+  using E = Elt<BF16>;
+  using vec8 = typename E::vec8;
+  using scalar = typename E::scalar;
+  __shared__ __attribute__((aligned(1024))) char k_s[2][kTileBytes];
+  __shared__ __attribute__((aligned(1024))) char v_s[2][kTileBytes];
+
+  const int item = work_item(a.order, a.B * a.H, np);
+  if (item < 0) return;
+  const int n = a.n, H = a.H, S = a.S;
+  const int ip = item % np;
+  const int bh = item / np;
+  const int h = bh % H, b = bh / H;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63;
+  const int l32 = lane & 31, hl = lane >> 5;
+  const int g = lane >> 4, j16 = lane & 15;
+
+  const uint16_t* kbase = static_cast<const uint16_t*>(a.k.data) + (int64_t)b * a.k.sb + (int64_t)h * a.k.sh;
+  const uint16_t* vbase = static_cast<const uint16_t*>(a.v.data) + (int64_t)b * a.v.sb + (int64_t)h * a.v.sh;
+  SharedTileLoader<NW> kl, vl;
+  kl.template init<true>(kbase, a.k.ss, wave, lane);
+  vl.template init<false>(vbase, a.v.ss, wave, lane);
+  const uint32_t klds = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)&k_s[0][0];
+  const uint32_t vlds = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)&v_s[0][0];
+  kl.template load<true>(klds, 0, S, wave);
+
+  const int qrow = (ip * NW + wave) * 32 + l32;
+  vec8 qf[8];
+  {
+    const uint16_t* qp = static_cast<const uint16_t*>(a.q.data) + (int64_t)b * a.q.sb + (int64_t)qrow * a.q.ss +
+                         (int64_t)h * a.q.sh + 8 * hl;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      if (qrow < S) {
+        qf[s] = *reinterpret_cast<const vec8*>(qp + 16 * s);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) qf[s][e] = (scalar)0.f;
+      }
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0xF70);   // vmcnt(0)
+  __syncthreads();
+  if (n > 1) kl.template load<true>(klds + kTileBytes, 1, S, wave);
+  vl.template load<false>(vlds, 0, S, wave);
+
+  const int k_row_off = l32 * 256;
+  const int k_swzl = l32 & 15;
+  const int v_lane_off = (j16 >> 2) * 256 + 8 * (j16 & 1) + 4 * (g >> 1) * 256;
+  const int v_c0 = 2 * (g & 1) + ((j16 & 3) >> 1);
+  const int v_sl = v_swz_bits(j16 >> 2);
+
+  const float cl2 = a.sm_scale * kLog2e;
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x16 o[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[u][r] = 0.f;
+
+  auto qk = [&](f32x16 (&s)[2], const char* kt) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[t][r] = 0.f;
+#pragma unroll
+    for (int d = 0; d < 8; ++d) {
+      const int koff = k_row_off + (((2 * d + hl) ^ k_swzl) << 4);
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+        s[t] = E::mfma(*reinterpret_cast<const vec8*>(kt + t * 32 * 256 + koff), qf[d], s[t]);
+    }
+  };
+  auto fix = [&](f32x16 (&s)[2], int j) {   // key scale and the end of the sequence
+    if (KSCALE && j * kBlock < a.ks.n_first) {
+      const int lim = a.ks.n_first - j * kBlock;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (32 * t + 8 * (r >> 2) + 4 * hl + (r & 3) < lim) s[t][r] *= a.ks.beta;
+    }
+    if (j * kBlock + kBlock > S) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (j * kBlock + 32 * t + 8 * (r >> 2) + 4 * hl + (r & 3) >= S) s[t][r] = -INFINITY;
+    }
+  };
+  auto row_max = [&](const f32x16 (&s)[2]) {
+    float mx = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[t][r]);
+    return pair_max(mx);
+  };
+  auto rescale = [&](float mx) {
+    const float m_new = fmaxf(m_run, mx * cl2);
+    if (__builtin_amdgcn_ballot_w64(m_new > m_run + kRescaleLog2) != 0) {
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+      m_run = m_new;
+      l_run *= alpha;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[u][r] *= alpha;
+    }
+  };
+  auto probs = [&](const f32x16 (&s)[2], vec8 (&pf)[2][2]) {
+    float rs = 0.f;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float p = __builtin_amdgcn_exp2f(s[t][r] * cl2 - m_run);
+        rs += p;
+        pf[t][r >> 3][r & 7] = (scalar)p;
+      }
+    l_run += rs;
+  };
+  auto pv = [&](const vec8 (&pf)[2][2], const char* vt) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int cu = (4 * u + v_c0) ^ v_sl;
+          const char* lo = vt + (32 * t + 16 * hh) * 256 + v_lane_off + (cu << 4);
+          const vec8 vf = E::tr_pair(lo, lo + 8 * 256);
+          o[u] = E::mfma(vf, pf[t][hh], o[u]);
+        }
+  };
+
+  f32x16 s0[2], s1[2];
+  qk(s0, k_s[0]);
+  fix(s0, 0);
+  float mx = row_max(s0);
+
+  // step j (fused): PV of block j, QK^T of block j + 1 beside its softmax
+  auto fused = [&](int j, int par, f32x16 (&sc)[2], f32x16 (&sn)[2]) {
+    CHORUS_WAIT_LDS_TILES();
+    __syncthreads();
+    if (j + 2 < n) kl.template load<true>(klds + par * kTileBytes, j + 2, S, wave);
+    vl.template load<false>(vlds + (par ^ 1) * kTileBytes, j + 1, S, wave);
+    rescale(mx);
+    vec8 pf[2][2];
+    qk(sn, k_s[par ^ 1]);
+    probs(sc, pf);
+    if (KSCALE) fix(sn, j + 1);
+    pv(pf, v_s[par]);
+    mx = row_max(sn);
+  };
+  int j = 0;
+  const int n_full = S / kBlock;
+  for (; j + 2 < n_full; j += 2) {
+    fused(j, 0, s0, s1);
+    fused(j + 1, 1, s1, s0);
+  }
+  for (; j < n; ++j) {
+    const int par = j & 1;
+    CHORUS_WAIT_LDS_TILES();
+    __syncthreads();
+    if (j + 2 < n) kl.template load<true>(klds + par * kTileBytes, j + 2, S, wave);
+    if (j + 1 < n) vl.template load<false>(vlds + (par ^ 1) * kTileBytes, j + 1, S, wave);
+    rescale(mx);
+    vec8 pf[2][2];
+    probs(s0, pf);
+    pv(pf, v_s[0] + par * kTileBytes);
+    if (j + 1 < n) {
+      qk(s0, k_s[0] + (par ^ 1) * kTileBytes);
+      fix(s0, j + 1);
+      mx = row_max(s0);
+    }
+  }
+
+  const float l_tot = pair_sum(l_run);
+  const bool live = l_tot > 0.f;
+  const float inv_l = live ? 1.f / l_tot : 0.f;
+  if (qrow < S) {
+    uint16_t* op = static_cast<uint16_t*>(const_cast<void*>(a.o.data)) + (int64_t)b * a.o.sb +
+                   (int64_t)qrow * a.o.ss + (int64_t)h * a.o.sh;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int rr = 0; rr < 4; ++rr) {
+        scalar v4[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v4[e] = (scalar)(o[u][4 * rr + e] * inv_l);
+        uint2 packed;
+        __builtin_memcpy(&packed, v4, 8);
+        *reinterpret_cast<uint2*>(op + 32 * u + 8 * rr + 4 * hl) = packed;
+      }
+    if (a.lse && hl == 0)
+      a.lse[((int64_t)b * H + h) * S + qrow] = live ? (m_run + __builtin_log2f(l_tot)) * kLn2 : -INFINITY;
+  }
+}
+
 }  // namespace
 
 namespace {
-template <bool BF16, bool DENSE, bool KV2>
-void launch_16(const AttnArgs& a, dim3 grid, hipStream_t st) {
+template <bool BF16, bool KV2>
+void launch_16(const AttnArgs& a, hipStream_t st) {
+  const dim3 grid(work_grid(a.B * a.H, a.n));
   if (a.ks.n_first > 0)
-    hipLaunchKernelGGL((attn_fwd_16_kernel<BF16, DENSE, true, KV2>), grid, dim3(128), 0, st, a);
+    hipLaunchKernelGGL((attn_fwd_16_kernel<BF16, true, KV2>), grid, dim3(128), 0, st, a);
   else
-    hipLaunchKernelGGL((attn_fwd_16_kernel<BF16, DENSE, false, KV2>), grid, dim3(128), 0, st, a);
+    hipLaunchKernelGGL((attn_fwd_16_kernel<BF16, false, KV2>), grid, dim3(128), 0, st, a);
+}
+
+template <bool BF16, int NW>
+void launch_dense_nw(const AttnArgs& a, hipStream_t st) {
+  const int np = (a.S + 32 * NW - 1) / (32 * NW);
+  const dim3 grid(work_grid(a.B * a.H, np)), block(64 * NW);
+  if (a.ks.n_first > 0)
+    hipLaunchKernelGGL((attn_dense_16_kernel<BF16, true, NW>), grid, block, 0, st, a, np);
+  else
+    hipLaunchKernelGGL((attn_dense_16_kernel<BF16, false, NW>), grid, block, 0, st, a, np);
+}
+
+// Waves per workgroup of the dense kernel: more waves share a tile, fewer
+// leave smaller pieces for the CUs (each CU holds eight such waves).  With
+// four rounds of eight-wave workgroups over the 256 CUs the sharing wins (480p
+// 14B: 17.9 against 19.0 ms); below that the uneven last round costs more
+// (S = 8,215, 3 heads: 0.204 ms with eight waves, 0.164 with four).  Two waves
+// were slower even there (0.236 ms).
+template <bool BF16>
+void launch_dense(const AttnArgs& a, hipStream_t st) {
+  const int64_t rows32 = (int64_t)a.B * a.H * ((a.S + 31) / 32);
+  if (rows32 >= 4 * 256 * 8)
+    launch_dense_nw<BF16, 8>(a, st);
+  else
+    launch_dense_nw<BF16, 4>(a, st);
 }
 
 template <bool BF16>
-void launch_16_mask(const AttnArgs& a, dim3 grid, hipStream_t st) {
+void launch_16_mask(const AttnArgs& a, hipStream_t st) {
   if (a.row_ptr == nullptr)
-    launch_16<BF16, true, false>(a, grid, st);
+    launch_dense<BF16>(a, st);
   else if (a.kv_block == 2 * kBlock)
-    launch_16<BF16, false, true>(a, grid, st);
+    launch_16<BF16, true>(a, st);
   else
-    launch_16<BF16, false, false>(a, grid, st);
+    launch_16<BF16, false>(a, st);
 }
 }  // namespace
 
 hipError_t launch_attn_fwd_16(chorus_dtype dt, const AttnArgs& a, hipStream_t st) {
-  const dim3 grid(work_grid(a.B * a.H, a.n));
   if (dt == CHORUS_BF16)
-    launch_16_mask<true>(a, grid, st);
+    launch_16_mask<true>(a, st);
   else
-    launch_16_mask<false>(a, grid, st);
+    launch_16_mask<false>(a, st);
   return hipGetLastError();
 }
 

@@ -224,9 +224,7 @@ void block_mass_kernel(TensorArg q, TensorArg k, const float* __restrict__ lse, 
       acc[x] = 0.f;
       const int j = j0 + x;
       if (j >= n) continue;
-      // K_j landed; the sums this wave published are in LDS (waited for by hand:
-      // the compiler's own wait was missing on the loop's back edge)
-      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+      CHORUS_WAIT_LDS_TILES();   // K_j landed; the sums this wave published are in LDS
       __syncthreads();
       if (j + 1 < n) load_k_share(lds0 + ((x + 1) & 1) * kMassTile, kbase, kss, koff_lane, j + 1, S, wave, lane);
       if (x == 0 && j0 > 0 && j0 % kMassGroup == 0) flush(j0 / kMassGroup - 1);
@@ -237,7 +235,7 @@ void block_mass_kernel(TensorArg q, TensorArg k, const float* __restrict__ lse, 
     }
     publish(acc, j0);
   }
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  CHORUS_WAIT_LDS_TILES();
   __syncthreads();
   flush((n - 1) / kMassGroup);
 }

@@ -285,6 +285,26 @@ def test_attention_without_mask_is_the_full_density_mask(dtype, key_scale):
     assert within_rounding(np64(dense), O, tdt, atol=tol), float(np.max(np.abs(np64(dense) - O)))
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("B,S,H", [(1, 1, 1), (1, 64, 3), (2, 129, 2), (1, 511, 8), (3, 193, 90), (2, 320, 64), (1, 850, 17),
+                                   (16, 260, 64), (8, 383, 90), (8, 850, 40)])
+def test_dense_kernel_variants_are_bitwise_the_full_mask(dtype, B, S, H):
+    """The dense kernel runs with four or eight waves per workgroup by the
+    amount of work, in pipelined and single steps by the number of full kv
+    blocks: every variant, with sequence ends inside and at the edge of a
+    workgroup's rows, gives the bits and the LSE of the masked kernel under an
+    explicit full mask."""
+    gen = torch.Generator(device="cuda").manual_seed(S)
+    q, k, v = (torch.randn(B, S, H, 128, generator=gen, device="cuda").to(dtype) for _ in range(3))
+    n = (S + 63) // 64
+    # up to 14 kv blocks every masked walk starts at block 0, as the dense one does
+    full = ops.BlockMask.from_host(np.arange(H * n + 1) * n, np.tile(np.arange(n), H * n), 1, H, n)
+    for key_scale in (None, (min(S, 100), 1.5)):
+        out, lse = ops.block_sparse_attn_fwd(q, k, v, None, return_lse=True, key_scale=key_scale)
+        ref, ref_lse = ops.block_sparse_attn_fwd(q, k, v, full, return_lse=True, key_scale=key_scale)
+        assert torch.equal(lse, ref_lse) and torch.equal(out.view(torch.int16), ref.view(torch.int16))
+
+
 def test_attention_strided_views_and_determinism():
     gen = torch.Generator().manual_seed(9)
     B, S, H = 2, 500, 2
