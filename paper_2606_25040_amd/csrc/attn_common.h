@@ -128,6 +128,43 @@ __device__ inline void dma16(uint32_t lds, const void* sbase, uint32_t voff) {
       : "memory");
 }
 
+// Four such loads from one base, 2 KB apart in LDS.
+__device__ inline void dma16x4(uint32_t lds, const void* sbase, const uint32_t (&voff)[4]) {
+  uint32_t saved;
+  asm volatile(
+      "s_mov_b32 %0, m0\n\t"
+      "s_mov_b32 m0, %1\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %2, %6\n\t"
+      "s_add_u32 m0, m0, 0x800\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %3, %6\n\t"
+      "s_add_u32 m0, m0, 0x800\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %4, %6\n\t"
+      "s_add_u32 m0, m0, 0x800\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %5, %6\n\t"
+      "s_mov_b32 m0, %0"
+      : "=&s"(saved)
+      : "s"(lds), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(sbase)
+      : "memory", "scc");
+}
+
+// walk_rotation over ascending ids, counted by the whole wave: the list is
+// read in coalesced runs instead of by dependent scalar loads.
+template <bool KV2>
+__device__ inline int walk_rotation_wave(const int32_t* col, int p0, int p1, int target) {
+  int below = 0;
+  const int lane = threadIdx.x & 63;
+  for (int p = p0 + lane; p - lane < p1; p += 64) {
+    const int id = p < p1 ? (KV2 ? 2 * col[p >> 1] + (p & 1) : col[p]) : INT32_MAX;
+    below += (int)__popcll(__builtin_amdgcn_ballot_w64(id < target));
+  }
+  below = __builtin_amdgcn_readfirstlane(below);
+  return below == p1 - p0 ? 0 : below;
+}
+
 // Wait until at most n vector-memory loads of this wave are outstanding.
 #define CHORUS_WAIT_VMCNT(n) asm volatile("s_waitcnt vmcnt(" #n ")" ::: "memory")
 

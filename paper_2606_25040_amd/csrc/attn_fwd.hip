@@ -3,23 +3,37 @@
 //
 // One workgroup = one work item (request b, head h, 64-query block i), two
 // waves of 32 queries, 32 KB of LDS, so four workgroups (two waves per SIMD)
-// share a CU and hide each other's latencies.  For each listed kv block j:
-//   * the list is walked from a rotated start (walk_target), so the q-blocks
-//     in flight on an XCD read about the same kv blocks at the same time;
-//   * K_j and V_j go global -> LDS with global_load_lds_dwordx4 (no register
-//     staging); each tile has its own single buffer, refilled as soon as the
-//     phase that reads it is over (K after QK^T, V after PV), so the next
-//     block's loads overlap this block's softmax and PV;
-//   * S^T = K_j Q^T with v_mfma_f32_32x32x16 (A = K rows from LDS, B = Q
-//     fragments kept in registers): each lane holds 32 scores of ONE query
-//     (lanes l and l ^ 32 split its 64 keys), so the row max and row sum are
-//     lane-local plus one half-wave exchange;
-//   * online softmax in the log2 domain; the running max is only moved (and
-//     O, l rescaled) when some row's max grew by more than kRescaleLog2, so
-//     P <= 2^kRescaleLog2 and most blocks skip the 64-register rescale;
-//   * O^T += V_j^T P^T with the same MFMA; V^T fragments come from the
-//     row-major tile through ds_read_b64_tr_b16; P is the score accumulator
-//     converted to 16-bit in registers.
+// share a CU.  The listed kv blocks are walked from a rotated start
+// (walk_target), so the q-blocks in flight on an XCD read about the same kv
+// blocks at the same time.  For each listed block j the wave works in two
+// steps, one per 32-key half of the block:
+//   * S^T = K Q^T of that half of the NEXT listed block, with
+//     v_mfma_f32_32x32x16 (A = K rows from LDS, B = Q fragments kept in
+//     registers): each lane holds scores of ONE query (lanes l and l ^ 32
+//     split the keys), so the row max and row sum are lane-local plus one
+//     half-wave exchange;
+//   * beside those products, which need nothing of block j, the probabilities
+//     of this half of block j: online softmax in the log2 domain; the running
+//     max is only moved (and O, l rescaled) when some row's max grew by more
+//     than kRescaleLog2, so P <= 2^kRescaleLog2 and most blocks skip the
+//     64-register rescale;
+//   * O^T += V^T P^T of the half with the same MFMA; V^T fragments come from
+//     the row-major tile through ds_read_b64_tr_b16; P is the score
+//     accumulator converted to 16-bit in registers.
+// K and V halves (8 KB) go global -> LDS with global_load_lds_dwordx4 (no
+// register staging) into two buffers each, so a half is requested a whole step
+// before it is read; one barrier per step.  After the last listed block the
+// products for a next one run on stale tiles and are not used, which costs
+// less than a second copy of the loop body (whose registers spill).
+// What bounds it: the tile feed (L2 misses, and the clock under that load)
+// and the vector instructions beside the MFMAs.  Same bits as the version that
+// ran QK^T, softmax and PV of a 64-key block one after the other on single
+// buffers, and faster: batch-4 480p 14B (bf16, 15 %) 14.09 against 15.00 ms,
+// 720p 5B (bf16, 20 %) 2.00 against 2.10 ms, f16 with kv blocks of 128 and a
+// key scale (2 x 16 heads, S = 17,523) 1.22 against 1.26 ms.  Measured beside
+// it: two q-blocks per workgroup walking the union of their lists 15.8 ms
+// (every fifth step has work for one of them only), separate waits for K and V
+// 15.60 against 15.17 ms, raised wave priority during QK^T 15.39.
 // LDS tiles are XOR-swizzled in 16-byte chunks (the direct loads permute the
 // global addresses instead of the LDS ones) so that the b128 K reads and the
 // transposed b64 V reads are bank-conflict free.
@@ -74,16 +88,16 @@ struct Elt<false> {
   }
 };
 
-// This wave's share of one 64 x 128 16-bit tile: instruction u fills LDS rows
+constexpr int kHalfBytes = kTileBytes / 2;   // 32 keys
+
+// This wave's share (one of two) of a 32 x 128 half tile: load u fills LDS rows
 // 8u + 4 wave .. + 3 (1 KB, lane-linear), each lane fetching the global chunk
-// that the swizzle places at its slot.  Full blocks take the row offset from
-// the scalar base and a per-lane offset fixed for the whole kernel; the
-// partial last block clamps rows past the sequence end to row S - 1 (their
-// keys are masked and their probabilities are zero).
-struct TileLoader {
-  const char* base;    // token 0 of this (b, h)
-  uint32_t ss;         // token stride in bytes
-  uint32_t off[2];     // lane offset for even / odd u (row r0, swizzled chunk)
+// that the swizzle places at its slot.  Full blocks add a per-lane offset
+// fixed for the whole kernel to the half's first row.
+struct HalfLoader {
+  const char* base;
+  uint32_t ss;
+  uint32_t off[4];
   int r0, p;
   template <bool IS_K>
   __device__ void init(const uint16_t* b, int64_t stride, int wave, int lane) {
@@ -92,38 +106,42 @@ struct TileLoader {
     r0 = 4 * wave + (lane >> 4);
     p = lane & 15;
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int c = IS_K ? k_swz(r0 + 8 * e, p) : v_swz(r0 + 8 * e, p);
-      off[e] = (uint32_t)r0 * ss + (uint32_t)c * 16;
+    for (int u = 0; u < 4; ++u) {
+      const int r = 8 * u + r0;
+      off[u] = (uint32_t)r * ss + (uint32_t)(IS_K ? k_swz(r, p) : v_swz(r, p)) * 16;
     }
   }
   template <bool IS_K>
-  __device__ void load(char* tile, int j, int S, int wave) const {
-    const uint32_t lds = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)tile + wave * 1024;
-    if (j * kBlock + kBlock <= S) {
-      const char* rowj = base + (int64_t)j * kBlock * ss;
+  __device__ void load(uint32_t lds, int j, int t, int S, int wave) const {
+    const int tok0 = j * kBlock + 32 * t;
+    uint32_t o[4];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) dma16(lds + u * 2048, rowj + (int64_t)(8 * u) * ss, off[u & 1]);
-    } else {
+    for (int u = 0; u < 4; ++u) o[u] = off[u];
+    const char* from = base + (int64_t)tok0 * ss;
+    if (j * kBlock + kBlock > S) {
+      // partial last block: rows past the end re-read row S - 1 (offsets from
+      // token 0: the half may start past the end)
+      from = base;
+      int pp = p, rr = r0;
+      asm volatile("" : "+v"(pp), "+v"(rr));   // computed here: kept across the loop it would cost registers
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int r = 8 * u + r0;
-        const int c = IS_K ? k_swz(r, p) : v_swz(r, p);
-        const int tok = min(j * kBlock + r, S - 1);
-        dma16(lds + u * 2048, base, (uint32_t)tok * ss + (uint32_t)c * 16);
+      for (int u = 0; u < 4; ++u) {
+        const int r = 8 * u + rr;
+        o[u] = (uint32_t)min(tok0 + r, S - 1) * ss + (uint32_t)(IS_K ? k_swz(r, pp) : v_swz(r, pp)) * 16;
       }
     }
+    dma16x4(lds + wave * 1024, from, o);
   }
 };
 
 template <bool BF16, bool KSCALE, bool KV2>
-__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_fwd_16_kernel(AttnArgs a) {
   using E = Elt<BF16>;
   using vec8 = typename E::vec8;
   using scalar = typename E::scalar;
-  __shared__ __attribute__((aligned(1024))) char k_s[kTileBytes];
-  __shared__ __attribute__((aligned(1024))) char v_s[kTileBytes];
+  __shared__ __attribute__((aligned(1024))) char k_s[2][kHalfBytes];
+  __shared__ __attribute__((aligned(1024))) char v_s[2][kHalfBytes];
 
   const int item = work_item(a.order, a.B * a.H, a.n);
   if (item < 0) return;
@@ -131,9 +149,6 @@ void attn_fwd_16_kernel(AttnArgs a) {
   const int i = item % n;
   const int bh = item / n;
   const int h = bh % H, b = bh / H;
-  // The CSR row of (b, h, i).  KV2: it lists kv blocks of 128 tokens and the
-  // walk visits both 64-token halves of each (positions 2 p and 2 p + 1 of the
-  // doubled list).
   const int64_t mrow = ((int64_t)(a.mask_batch > 1 ? b : 0) * H + h) * n + i;
   int kb0 = a.row_ptr[mrow], kb1 = a.row_ptr[mrow + 1];
   if (KV2) {
@@ -142,44 +157,43 @@ void attn_fwd_16_kernel(AttnArgs a) {
   }
   ConstI32* cidx = as_constant(a.col_idx);   // scalar loads
   auto kv_at = [&](int p) { return KV2 ? 2 * cidx[p >> 1] + (p & 1) : cidx[p]; };
-  // walk step v visits list position kb0 + (v + rot) mod L (see walk_target)
   const int L = kb1 - kb0;
-  const int rot = walk_rotation(kb0, kb1, walk_target(i, n), kv_at);
-  auto kv_block = [&](int v) {
-    const int p = v + rot;
-    return kv_at(kb0 + (p >= L ? p - L : p));
-  };
-  // ids outside [0, n) are skipped (the builder never emits them; with KV2
-  // this also drops the missing half of a last block of 64 tokens)
-  auto next_valid = [&](int jj) {
-    while (jj < L) {
-      const int j = kv_block(jj);
-      if (j >= 0 && j < n) break;
-      ++jj;
+  const int rot = walk_rotation_wave<KV2>(a.col_idx, kb0, kb1, walk_target(i, n));
+  // next listed block, the id after it read ahead
+  int left = L, pos = kb0 + rot;
+  int ahead = L > 0 ? kv_at(pos) : 0;
+  auto next = [&]() {
+    for (;;) {
+      if (left <= 0) return -1;
+      const int j = ahead;
+      --left;
+      ++pos;
+      if (pos == kb1) pos = kb0;
+      if (left > 0) ahead = kv_at(pos);
+      if ((unsigned)j < (unsigned)n) return j;
     }
-    return jj;
   };
 
   const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
   const int l32 = lane & 31, hl = lane >> 5;
   const int g = lane >> 4, j16 = lane & 15;
 
   const uint16_t* kbase = static_cast<const uint16_t*>(a.k.data) + (int64_t)b * a.k.sb + (int64_t)h * a.k.sh;
   const uint16_t* vbase = static_cast<const uint16_t*>(a.v.data) + (int64_t)b * a.v.sb + (int64_t)h * a.v.sh;
-
-  TileLoader kl, vl;
+  HalfLoader kl, vl;
   kl.init<true>(kbase, a.k.ss, wave, lane);
   vl.init<false>(vbase, a.v.ss, wave, lane);
-  int jj = next_valid(0);
-  if (jj < L) {
-    const int j0 = kv_block(jj);
-    kl.load<true>(k_s, j0, S, wave);
-    vl.load<false>(v_s, j0, S, wave);
+  const uint32_t klds = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)&k_s[0][0];
+  const uint32_t vlds = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)&v_s[0][0];
+  int jc = next();
+  if (jc >= 0) {
+    kl.load<true>(klds, jc, 0, S, wave);
+    kl.load<true>(klds + kHalfBytes, jc, 1, S, wave);
   }
+  int jn = next();
 
-  // Q^T fragments: query qrow, head-dim slice 16 s + 8 hl .. + 8
   const int qrow = i * kBlock + wave * 32 + l32;
   vec8 qf[8];
   {
@@ -195,78 +209,58 @@ void attn_fwd_16_kernel(AttnArgs a) {
       }
     }
   }
-  // Drain the Q loads (and the first tiles) with an s_waitcnt the compiler
-  // sees, so that it does not re-wait for Q inside the loop.
   __builtin_amdgcn_s_waitcnt(0xF70);   // vmcnt(0)
+  __syncthreads();
 
-  // per-lane LDS byte offsets of the K (A operand) and V^T (transposed) reads
   const int k_row_off = l32 * 256;
   const int k_swzl = l32 & 15;
-  const int v_lane_off = (j16 >> 2) * 256 + 8 * (j16 & 1);
+  const int v_lane_off = (j16 >> 2) * 256 + 8 * (j16 & 1) + 4 * (g >> 1) * 256;
   const int v_c0 = 2 * (g & 1) + ((j16 & 3) >> 1);
   const int v_sl = v_swz_bits(j16 >> 2);
 
   const float cl2 = a.sm_scale * kLog2e;
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = -INFINITY, l_run = 0.f, rs = 0.f;
   f32x16 o[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[u][r] = 0.f;
 
-  while (jj < L) {
-    const int j = kv_block(jj);
-    const int jn = next_valid(jj + 1);
-    const bool has_next = jn < L;
-    const int j_next = has_next ? kv_block(jn) : 0;
-
-    // K_j resident: at most this block's V loads (8) are still in flight
-    CHORUS_WAIT_VMCNT(8);
-    __syncthreads();
-    f32x16 sacc[2];
+  auto qk = [&](f32x16& s, const char* kt) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int r = 0; r < 16; ++r) s[r] = 0.f;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) sacc[t][r] = 0.f;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const int koff = k_row_off + (((2 * s + hl) ^ k_swzl) << 4);
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {       // two independent accumulation chains
-        const vec8 kf = *reinterpret_cast<const vec8*>(k_s + t * 32 * 256 + koff);
-        sacc[t] = E::mfma(kf, qf[s], sacc[t]);
-      }
-    }
-    __syncthreads();                               // every wave is done with K_j
-    if (has_next) kl.load<true>(k_s, j_next, S, wave);
-
-    // first-frame keys (Eq. 1): their logits count beta times
+    for (int d = 0; d < 8; ++d)
+      s = E::mfma(*reinterpret_cast<const vec8*>(kt + k_row_off + (((2 * d + hl) ^ k_swzl) << 4)), qf[d], s);
+  };
+  auto fix = [&](f32x16 (&s)[2], int j) {   // key scale (Eq. 1) and the end of the sequence
+    int hl4 = 4 * hl;
+    asm volatile("" : "+v"(hl4));   // the key indices are computed here each time
     if (KSCALE && j * kBlock < a.ks.n_first) {
       const int lim = a.ks.n_first - j * kBlock;
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = 32 * t + 8 * (r >> 2) + 4 * hl + (r & 3);
-          if (key < lim) sacc[t][r] *= a.ks.beta;
-        }
+        for (int r = 0; r < 16; ++r)
+          if (32 * t + 8 * (r >> 2) + hl4 + (r & 3) < lim) s[t][r] *= a.ks.beta;
     }
-    // keys at or beyond S (partial last block) carry no weight
     if (j * kBlock + kBlock > S) {
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = 32 * t + 8 * (r >> 2) + 4 * hl + (r & 3);
-          if (j * kBlock + key >= S) sacc[t][r] = -INFINITY;
-        }
+        for (int r = 0; r < 16; ++r)
+          if (j * kBlock + 32 * t + 8 * (r >> 2) + hl4 + (r & 3) >= S) s[t][r] = -INFINITY;
     }
+  };
+  auto row_max = [&](const f32x16 (&s)[2]) {
     float mx = -INFINITY;
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[t][r]);
-    mx = pair_max(mx);
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[t][r]);
+    return pair_max(mx);
+  };
+  auto rescale = [&](float mx) {
     const float m_new = fmaxf(m_run, mx * cl2);
     if (__builtin_amdgcn_ballot_w64(m_new > m_run + kRescaleLog2) != 0) {
       const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
@@ -277,43 +271,77 @@ void attn_fwd_16_kernel(AttnArgs a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[u][r] *= alpha;
     }
-    float rs = 0.f;
-    vec8 pf[2][2];
+  };
+  auto probs = [&](const f32x16& s, vec8 (&pf)[2]) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float p = __builtin_amdgcn_exp2f(sacc[t][r] * cl2 - m_run);
-        rs += p;
-        pf[t][r >> 3][r & 7] = (scalar)p;
-      }
-    l_run += rs;
-
-    // V_j resident: only the next K tile's loads (8, if issued) may be in flight
-    if (has_next) {
-      CHORUS_WAIT_VMCNT(8);
-    } else {
-      CHORUS_WAIT_VMCNT(0);
+    for (int r = 0; r < 16; ++r) {
+      const float p = __builtin_amdgcn_exp2f(s[r] * cl2 - m_run);
+      rs += p;
+      pf[r >> 3][r & 7] = (scalar)p;
     }
-    __syncthreads();
-    // O^T[u] += V^T[u] P^T: k-slot i of lane half hl maps to key
-    // 32 t + 16 hh + 8 (i / 4) + 4 hl + i % 4 in both operands.
+  };
+  auto pv = [&](const vec8 (&pf)[2], const char* vt) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        const int k0 = 32 * t + 16 * hh + 4 * (g >> 1);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {     // four independent accumulators
-          const int cu = (4 * u + v_c0) ^ v_sl;
-          const char* lo = v_s + k0 * 256 + v_lane_off + (cu << 4);
-          const vec8 vf = E::tr_pair(lo, lo + 8 * 256);
-          o[u] = E::mfma(vf, pf[t][hh], o[u]);
-        }
+      for (int u = 0; u < 4; ++u) {
+        const int cu = (4 * u + v_c0) ^ v_sl;
+        const char* lo = vt + 16 * hh * 256 + v_lane_off + (cu << 4);
+        const vec8 vf = E::tr_pair(lo, lo + 8 * 256);
+        o[u] = E::mfma(vf, pf[hh], o[u]);
       }
-    __syncthreads();                               // every wave is done with V_j
-    if (has_next) vl.load<false>(v_s, j_next, S, wave);
-    jj = jn;
+  };
+
+  f32x16 s0[2], s1[2];
+  float mx = -INFINITY;
+  if (jc >= 0) {
+    qk(s0[0], k_s[0]);
+    qk(s0[1], k_s[1]);
+    fix(s0, jc);
+    mx = row_max(s0);
+    CHORUS_WAIT_LDS_TILES();
+    __syncthreads();
+    vl.load<false>(vlds, jc, 0, S, wave);
+    if (jn >= 0) kl.load<true>(klds, jn, 0, S, wave);
+  }
+  // block jc: probabilities and PV, half by half, beside QK^T of the same half of block jn
+  auto step = [&](f32x16 (&sc)[2], f32x16 (&sn)[2]) {
+    const int j2 = next();
+    CHORUS_WAIT_LDS_TILES();
+    __syncthreads();
+    if (jn >= 0) kl.load<true>(klds + kHalfBytes, jn, 1, S, wave);
+    vl.load<false>(vlds + kHalfBytes, jc, 1, S, wave);
+    rescale(mx);
+    {
+      rs = 0.f;
+      vec8 pf[2];
+      qk(sn[0], k_s[0]);
+      probs(sc[0], pf);
+      pv(pf, v_s[0]);
+    }
+    CHORUS_WAIT_LDS_TILES();
+    __syncthreads();
+    if (j2 >= 0) kl.load<true>(klds, j2, 0, S, wave);
+    if (jn >= 0) vl.load<false>(vlds, jn, 0, S, wave);
+    {
+      vec8 pf[2];
+      qk(sn[1], k_s[1]);
+      probs(sc[1], pf);
+      pv(pf, v_s[1]);
+      l_run += rs;
+      mx = row_max(sn);
+    }
+    if (jn >= 0 && (KSCALE || jn * kBlock + kBlock > S)) {
+      fix(sn, jn);
+      mx = row_max(sn);
+    }
+    jc = jn;
+    jn = j2;
+  };
+  while (jc >= 0) {
+    step(s0, s1);
+    if (jc < 0) break;
+    step(s1, s0);
   }
 
   // epilogue: lane pair (l, l ^ 32) holds partial sums of the same query
