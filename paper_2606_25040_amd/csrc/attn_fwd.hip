@@ -38,11 +38,14 @@
 // global addresses instead of the LDS ones) so that the b128 K reads and the
 // transposed b64 V reads are bank-conflict free.
 // Epilogue: O = O^T / l written as 16-bit, lse = ln(sum exp) in fp32.
-// Template flags: KSCALE multiplies the logits of keys below n_first by beta
+// With P > 1 a workgroup of P wave pairs splits the row's walk into P runs, each
+// with tiles of its own, and part 0 merges the (m, l, O) of the others at the
+// end: for launches with too few rows to fill the chip (list_parts).
+// Template flags: DENSE walks every kv block; KSCALE multiplies the logits of keys below n_first by beta
 // (first-frame key enhancement, Eq. 1); KV2 reads a mask of 128-token kv blocks
 // and walks each as its two 64-token halves.  Each flag is its own
 // instantiation, so the plain path carries none of the others' work.
-// Without a mask attn_dense_16_kernel below runs instead.
+// Without a mask attn_dense_16_kernel below runs, except on small launches.
 #include "attn_common.h"
 
 namespace chorus {
@@ -134,14 +137,13 @@ struct HalfLoader {
   }
 };
 
-template <bool BF16, bool KSCALE, bool KV2>
-__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <bool BF16, bool DENSE, bool KSCALE, bool KV2, int P>
+__global__ __launch_bounds__(128 * P) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_fwd_16_kernel(AttnArgs a) {
   using E = Elt<BF16>;
   using vec8 = typename E::vec8;
   using scalar = typename E::scalar;
-  __shared__ __attribute__((aligned(1024))) char k_s[2][kHalfBytes];
-  __shared__ __attribute__((aligned(1024))) char v_s[2][kHalfBytes];
+  __shared__ __attribute__((aligned(1024))) char kv_s[P][4][kHalfBytes];   // per part: two K halves, two V halves
 
   const int item = work_item(a.order, a.B * a.H, a.n);
   if (item < 0) return;
@@ -149,19 +151,38 @@ void attn_fwd_16_kernel(AttnArgs a) {
   const int i = item % n;
   const int bh = item / n;
   const int h = bh % H, b = bh / H;
-  const int64_t mrow = ((int64_t)(a.mask_batch > 1 ? b : 0) * H + h) * n + i;
-  int kb0 = a.row_ptr[mrow], kb1 = a.row_ptr[mrow + 1];
-  if (KV2) {
-    kb0 *= 2;
-    kb1 *= 2;
-  }
+  // The CSR row of (b, h, i) (DENSE: every kv block).  KV2: it lists kv blocks
+  // of 128 tokens and the walk visits both 64-token halves of each (positions
+  // 2 p and 2 p + 1 of the doubled list, without a missing second half at its
+  // end).
+  int kb0 = 0, kb1 = n;
   ConstI32* cidx = as_constant(a.col_idx);   // scalar loads
-  auto kv_at = [&](int p) { return KV2 ? 2 * cidx[p >> 1] + (p & 1) : cidx[p]; };
+  auto kv_at = [&](int p) { return DENSE ? p : KV2 ? 2 * cidx[p >> 1] + (p & 1) : cidx[p]; };
+  if (!DENSE) {
+    const int64_t mrow = ((int64_t)(a.mask_batch > 1 ? b : 0) * H + h) * n + i;
+    kb0 = a.row_ptr[mrow];
+    kb1 = a.row_ptr[mrow + 1];
+    if (KV2) {
+      kb0 *= 2;
+      kb1 *= 2;
+      if (kb1 > kb0 && kv_at(kb1 - 1) == n) --kb1;
+    }
+  }
+  const int tid = threadIdx.x;
+  const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = wave_id & 1, part = wave_id >> 1;   // query half, share of the list
   const int L = kb1 - kb0;
-  const int rot = walk_rotation_wave<KV2>(a.col_idx, kb0, kb1, walk_target(i, n));
-  // next listed block, the id after it read ahead
-  int left = L, pos = kb0 + rot;
-  int ahead = L > 0 ? kv_at(pos) : 0;
+  int left = L, pos = kb0;
+  if (!DENSE && L > 0) pos += walk_rotation_wave<KV2>(a.col_idx, kb0, kb1, walk_target(i, n));
+  if (P > 1) {   // this part's run of the walk
+    const int w0 = (int)((int64_t)part * L / P);
+    left = (int)((int64_t)(part + 1) * L / P) - w0;
+    pos += w0;
+    if (pos >= kb1) pos -= L;
+  }
+  // next listed block (-1 when done), the id after it read ahead; ids outside
+  // [0, n) are skipped (the builder never emits them)
+  int ahead = left > 0 ? kv_at(pos) : 0;
   auto next = [&]() {
     for (;;) {
       if (left <= 0) return -1;
@@ -174,8 +195,6 @@ void attn_fwd_16_kernel(AttnArgs a) {
     }
   };
 
-  const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
   const int l32 = lane & 31, hl = lane >> 5;
   const int g = lane >> 4, j16 = lane & 15;
@@ -185,8 +204,10 @@ void attn_fwd_16_kernel(AttnArgs a) {
   HalfLoader kl, vl;
   kl.init<true>(kbase, a.k.ss, wave, lane);
   vl.init<false>(vbase, a.v.ss, wave, lane);
-  const uint32_t klds = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)&k_s[0][0];
-  const uint32_t vlds = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)&v_s[0][0];
+  char(*k_s)[kHalfBytes] = &kv_s[P > 1 ? part : 0][0];
+  char(*v_s)[kHalfBytes] = &kv_s[P > 1 ? part : 0][2];
+  const uint32_t klds = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)k_s;
+  const uint32_t vlds = klds + 2 * kHalfBytes;
   int jc = next();
   if (jc >= 0) {
     kl.load<true>(klds, jc, 0, S, wave);
@@ -299,20 +320,23 @@ void attn_fwd_16_kernel(AttnArgs a) {
     qk(s0[1], k_s[1]);
     fix(s0, jc);
     mx = row_max(s0);
-    CHORUS_WAIT_LDS_TILES();
-    __syncthreads();
+  }
+  CHORUS_WAIT_LDS_TILES();
+  __syncthreads();
+  if (jc >= 0) {
     vl.load<false>(vlds, jc, 0, S, wave);
     if (jn >= 0) kl.load<true>(klds, jn, 0, S, wave);
   }
-  // block jc: probabilities and PV, half by half, beside QK^T of the same half of block jn
+  // block jc: probabilities and PV, half by half, beside QK^T of the same half
+  // of block jn.  With P > 1 a part that is done only keeps the barriers.
   auto step = [&](f32x16 (&sc)[2], f32x16 (&sn)[2]) {
     const int j2 = next();
     CHORUS_WAIT_LDS_TILES();
     __syncthreads();
-    if (jn >= 0) kl.load<true>(klds + kHalfBytes, jn, 1, S, wave);
-    vl.load<false>(vlds + kHalfBytes, jc, 1, S, wave);
-    rescale(mx);
-    {
+    if (P == 1 || jc >= 0) {
+      if (jn >= 0) kl.load<true>(klds + kHalfBytes, jn, 1, S, wave);
+      vl.load<false>(vlds + kHalfBytes, jc, 1, S, wave);
+      rescale(mx);
       rs = 0.f;
       vec8 pf[2];
       qk(sn[0], k_s[0]);
@@ -321,31 +345,90 @@ void attn_fwd_16_kernel(AttnArgs a) {
     }
     CHORUS_WAIT_LDS_TILES();
     __syncthreads();
-    if (j2 >= 0) kl.load<true>(klds, j2, 0, S, wave);
-    if (jn >= 0) vl.load<false>(vlds, jn, 0, S, wave);
-    {
+    if (P == 1 || jc >= 0) {
+      if (j2 >= 0) kl.load<true>(klds, j2, 0, S, wave);
+      if (jn >= 0) vl.load<false>(vlds, jn, 0, S, wave);
       vec8 pf[2];
       qk(sn[1], k_s[1]);
       probs(sc[1], pf);
       pv(pf, v_s[1]);
       l_run += rs;
       mx = row_max(sn);
-    }
-    if (jn >= 0 && (KSCALE || jn * kBlock + kBlock > S)) {
-      fix(sn, jn);
-      mx = row_max(sn);
+      if (jn >= 0 && (KSCALE || jn * kBlock + kBlock > S)) {
+        fix(sn, jn);
+        mx = row_max(sn);
+      }
     }
     jc = jn;
     jn = j2;
   };
-  while (jc >= 0) {
-    step(s0, s1);
-    if (jc < 0) break;
-    step(s1, s0);
+  if (P == 1) {
+    while (jc >= 0) {
+      step(s0, s1);
+      if (jc < 0) break;
+      step(s1, s0);
+    }
+  } else {
+    const int steps = (L + P - 1) / P;   // of the longest part
+    for (int x = 0; x < steps; ++x) {
+      step(s0, s1);
+      if (++x >= steps) break;
+      step(s1, s0);
+    }
   }
 
-  // epilogue: lane pair (l, l ^ 32) holds partial sums of the same query
-  const float l_tot = pair_sum(l_run);
+  float l_tot = pair_sum(l_run);   // lane pair (l, l ^ 32) holds partial sums of the same query
+  if (P > 1) {
+    // Parts 1 .. P - 1 hand their (m, l, O) to part 0 through the tiles.
+    float* mine = reinterpret_cast<float*>(&kv_s[part][0][0]);
+    __shared__ float ml[P][2][2][32];   // [part][query half][m, l][query]
+    CHORUS_WAIT_LDS_TILES();
+    __syncthreads();
+    if (part > 0) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr)
+          reinterpret_cast<float4*>(mine)[((4 * u + rr) * 2 + wave) * 64 + lane] =
+              make_float4(o[u][4 * rr], o[u][4 * rr + 1], o[u][4 * rr + 2], o[u][4 * rr + 3]);
+      if (hl == 0) {
+        ml[part][wave][0][l32] = m_run;
+        ml[part][wave][1][l32] = l_tot;
+      }
+    }
+    CHORUS_WAIT_LDS_TILES();
+    __syncthreads();
+    if (part > 0) return;
+    float m_all = m_run;
+#pragma unroll
+    for (int x = 1; x < P; ++x) m_all = fmaxf(m_all, ml[x][wave][0][l32]);
+    // a part without blocks has m = -inf and nothing to add
+    auto weight = [&](float m) { return m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - m_all); };
+    const float f0 = weight(m_run);
+    l_tot *= f0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[u][r] *= f0;
+#pragma unroll
+    for (int x = 1; x < P; ++x) {
+      const float f = weight(ml[x][wave][0][l32]);
+      l_tot += f * ml[x][wave][1][l32];
+      const float4* their = reinterpret_cast<const float4*>(&kv_s[x][0][0]);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) {
+          const float4 t = their[((4 * u + rr) * 2 + wave) * 64 + lane];
+          o[u][4 * rr] += f * t.x;
+          o[u][4 * rr + 1] += f * t.y;
+          o[u][4 * rr + 2] += f * t.z;
+          o[u][4 * rr + 3] += f * t.w;
+        }
+    }
+    m_run = m_all;
+  }
+
   const bool live = kb1 > kb0 && l_tot > 0.f;
   const float inv_l = live ? 1.f / l_tot : 0.f;
   if (qrow < S) {
@@ -623,13 +706,27 @@ void attn_dense_16_kernel(AttnArgs a, int np) {
 }  // namespace
 
 namespace {
-template <bool BF16, bool KV2>
+template <bool BF16, bool DENSE, bool KV2, int P>
 void launch_16(const AttnArgs& a, hipStream_t st) {
-  const dim3 grid(work_grid(a.B * a.H, a.n));
+  const dim3 grid(work_grid(a.B * a.H, a.n)), block(128 * P);
   if (a.ks.n_first > 0)
-    hipLaunchKernelGGL((attn_fwd_16_kernel<BF16, true, KV2>), grid, dim3(128), 0, st, a);
+    hipLaunchKernelGGL((attn_fwd_16_kernel<BF16, DENSE, true, KV2, P>), grid, block, 0, st, a);
   else
-    hipLaunchKernelGGL((attn_fwd_16_kernel<BF16, false, KV2>), grid, dim3(128), 0, st, a);
+    hipLaunchKernelGGL((attn_fwd_16_kernel<BF16, DENSE, false, KV2, P>), grid, block, 0, st, a);
+}
+
+// Parts a row's list is split into.  A workgroup with P parts takes P times the
+// LDS, so a CU holds four (P = 1), two or one of them; a split pays while the
+// rows alone leave that room empty.  One row per CU or fewer: four parts
+// (4,096 tokens, 2 heads, f16: 22 us, unsplit 35); two per CU or fewer: two
+// (3,900 tokens, 5 heads: 27 us, four parts 37, unsplit 38).  Beyond that the
+// rows fill the chip (3,900 tokens, 10 heads: 42 us either way).  Dense calls
+// of that size run here too, 3,120 tokens x 4 heads: 35 us against 53 with
+// attn_dense_16_kernel.  The rule reads sizes only, so a full mask and no mask
+// take the same split.
+int list_parts(const AttnArgs& a) {
+  const int64_t rows = (int64_t)a.B * a.H * a.n;
+  return rows <= 256 ? 4 : rows <= 512 ? 2 : 1;
 }
 
 template <bool BF16, int NW>
@@ -657,14 +754,28 @@ void launch_dense(const AttnArgs& a, hipStream_t st) {
     launch_dense_nw<BF16, 4>(a, st);
 }
 
+template <bool BF16, bool DENSE, bool KV2>
+void launch_parts(const AttnArgs& a, int parts, hipStream_t st) {
+  if (parts == 4)
+    launch_16<BF16, DENSE, KV2, 4>(a, st);
+  else
+    launch_16<BF16, DENSE, KV2, 2>(a, st);
+}
+
 template <bool BF16>
 void launch_16_mask(const AttnArgs& a, hipStream_t st) {
-  if (a.row_ptr == nullptr)
-    launch_dense<BF16>(a, st);
-  else if (a.kv_block == 2 * kBlock)
-    launch_16<BF16, true>(a, st);
-  else
-    launch_16<BF16, false>(a, st);
+  const int parts = list_parts(a);
+  const bool kv2 = a.kv_block == 2 * kBlock;
+  if (a.row_ptr == nullptr) {
+    if (parts > 1)
+      launch_parts<BF16, true, false>(a, parts, st);
+    else
+      launch_dense<BF16>(a, st);
+  } else if (parts > 1) {
+    kv2 ? launch_parts<BF16, false, true>(a, parts, st) : launch_parts<BF16, false, false>(a, parts, st);
+  } else {
+    kv2 ? launch_16<BF16, false, true, 1>(a, st) : launch_16<BF16, false, false, 1>(a, st);
+  }
 }
 }  // namespace
 

@@ -305,6 +305,37 @@ def test_dense_kernel_variants_are_bitwise_the_full_mask(dtype, B, S, H):
         assert torch.equal(lse, ref_lse) and torch.equal(out.view(torch.int16), ref.view(torch.int16))
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("kv_block", [64, 128])
+@pytest.mark.parametrize("key_scale", [None, (700, 1.5)])
+@pytest.mark.parametrize("H,S", [(16, 1000), (17, 960), (32, 1000), (33, 960), (40, 970)])
+def test_attention_in_list_parts_matches_oracle(dtype, kv_block, key_scale, H, S):
+    """Rows split into four (up to 256 rows), two (up to 512) or no parts: rows
+    shorter than the number of parts, empty rows, ids outside [0, n_kv) and a
+    missing second half at the end, first and last head against the oracle."""
+    gen = torch.Generator().manual_seed(H)
+    q, k, v = rand_qkv(gen, 1, S, H, dtype)
+    n, nk = (S + 63) // 64, (S + kv_block - 1) // kv_block
+    rng = np.random.Generator(np.random.PCG64(H + S))
+    rp, ci = wk.random_csr(rng, H * n, nk, 0.4, empty_frac=0.15)
+    rows = [np.concatenate([[-1], ci[rp[r]:rp[r + 1]], [nk]]) if r % 4 == 3 else ci[rp[r]:rp[r + 1]]
+            for r in range(H * n)]
+    mask = ops.BlockMask.from_host(np.concatenate([[0], np.cumsum([len(x) for x in rows])]), np.concatenate(rows), 1, H,
+                                   n, block=kv_block)
+    out, lse = ops.block_sparse_attn_fwd(q.cuda(), k.cuda(), v.cuda(), mask, return_lse=True, key_scale=key_scale)
+    for h in (0, H - 1):
+        kk = np64(k[:, :, h:h + 1])
+        kk = kk if key_scale is None else og.enhance_first_frame_keys(kk, *key_scale)
+        a, b = rp[h * n], rp[(h + 1) * n]
+        O, L = oa.attention(np64(q[:, :, h:h + 1]), kk, np64(v[:, :, h:h + 1]), rp[h * n:(h + 1) * n + 1] - a, ci[a:b],
+                            1.0 / math.sqrt(128), 1, kv_block=kv_block)
+        assert within_rounding(np64(out[:, :, h:h + 1]), O, dtype, atol=TOL16)
+        got = lse[:, h:h + 1].cpu().numpy()
+        assert np.array_equal(np.isfinite(got), np.isfinite(L))
+        fin = np.isfinite(L)
+        assert np.max(np.abs(got[fin] - L[fin])) <= 1e-3
+
+
 def test_attention_strided_views_and_determinism():
     gen = torch.Generator().manual_seed(9)
     B, S, H = 2, 500, 2
