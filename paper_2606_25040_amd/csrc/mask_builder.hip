@@ -175,84 +175,93 @@ __global__ __launch_bounds__(kHeadDim) void means_from_sums_kernel(const double*
 // ---------------------------------------------------------------------------
 // 2a. Block scores s = sm_scale * qbar kbar^T per (request, head), n x nk
 // (q-blocks x kv blocks): a float64 GEMM on the matrix cores
-// (v_mfma_f64_16x16x4f64), one 128 x 128 output tile per workgroup of eight
-// waves, each wave a 64 x 32 eighth as 4 x 2 MFMA tiles (112 registers, so a
-// SIMD holds four such waves: two workgroups per CU).  The head dim is
-// staged through LDS sixteen at a time (both operands k-major, so a lane's
-// fragment is one float64 of a row); the next chunk is fetched into
-// registers while the current one is multiplied.  Writes float64 scores
-// into the workspace and, optionally, fp32 copies.
+// (v_mfma_f64_16x16x4f64), one ST x ST output tile per workgroup, each wave
+// 16 TA x 32 of it as TA x 2 MFMA tiles.  The head dim is staged through LDS
+// SK at a time (both operands k-major, so a lane's fragment is one float64 of
+// a row); the next chunk is fetched into registers while the current one is
+// multiplied.  Writes float64 scores into the workspace and, optionally, fp32
+// copies.  An element is the same chain of products whatever the tile, so the
+// scores are the same bits.
+// What bounds it: the fp64 matrix rate (64 cycles per MFMA), so a tile of 128
+// keeps one CU busy for 22 us however small the launch, and its padding and
+// uneven last round count.  Tiles of 64 (SK 16) against 128: 74 blocks x 12
+// heads 11.0 against 24.3 us, 317 x 24 22.3 against 28.6, 512 x 40 63.6
+// against 72.2, 1,182 x 40 293 against 318.  The staging writes conflict in
+// LDS when SK grows (SK 32: 91 us at 512 x 40); row paddings of 4 or 16
+// instead of 2 and SK 8 are no faster.
 // ---------------------------------------------------------------------------
-constexpr int kST = 128;  // score tile
-constexpr int kSK = 16;   // k-chunk
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(512) void score_kernel(const double* __restrict__ qbar,
-                                                    const double* __restrict__ kbar, int n, int nk, double sm_scale,
-                                                    double* __restrict__ scores, float* __restrict__ scores32) {
-  __shared__ double qs[kSK][kST + 2];
-  __shared__ double ks[kSK][kST + 2];
+template <int ST, int SK, int WR, int TA>
+__global__ __launch_bounds__(4 * ST) void score_kernel(const double* __restrict__ qbar,
+                                                       const double* __restrict__ kbar, int n, int nk, double sm_scale,
+                                                       double* __restrict__ scores, float* __restrict__ scores32) {
+  __shared__ double qs[SK][ST + 2];
+  __shared__ double ks[SK][ST + 2];
   const int bh = blockIdx.z;
-  const int i0 = blockIdx.y * kST, j0 = blockIdx.x * kST;
+  const int i0 = blockIdx.y * ST, j0 = blockIdx.x * ST;
   const double* qb = qbar + (int64_t)bh * n * kHeadDim;
   const double* kb = kbar + (int64_t)bh * nk * kHeadDim;
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63;
-  const int wr = wave >> 2, wc = wave & 3;   // 64-row half, 32-column quarter
+  constexpr int kWC = ST / 32, kWaveRows = 16 * TA;
+  static_assert(WR * kWaveRows == ST && WR * kWC * 64 == 4 * ST, "the waves cover the tile");
+  const int wr = wave / kWC, wc = wave % kWC;   // kWaveRows x 32 of the tile
   const int li = lane & 15, lk = lane >> 4;
-  const bool wave_live = i0 + wr * 64 < n && j0 + wc * 32 < nk;
-  // staging: thread -> (row r, dims d0 .. d0 + 3) of each operand's chunk
-  const int sr = tid >> 2, sd0 = (tid & 3) * 4;
+  const bool wave_live = i0 + wr * kWaveRows < n && j0 + wc * 32 < nk;
+  // staging: thread -> (row r, dims d0 .. d0 + kD - 1) of each operand's chunk
+  constexpr int kD = SK / 4;
+  const int sr = tid >> 2, sd0 = (tid & 3) * kD;
   const bool qin = i0 + sr < n, kin = j0 + sr < nk;
   const double* qrow = qb + (int64_t)(qin ? i0 + sr : 0) * kHeadDim + sd0;
   const double* krow = kb + (int64_t)(kin ? j0 + sr : 0) * kHeadDim + sd0;
-  double qv[4], kv[4];
+  double qv[kD], kv[kD];
 #pragma unroll
-  for (int d = 0; d < 4; ++d) {
+  for (int d = 0; d < kD; ++d) {
     qv[d] = qin ? qrow[d] : 0.0;
     kv[d] = kin ? krow[d] : 0.0;
   }
-  f64x4 acc[4][2];
+  f64x4 acc[TA][2];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < TA; ++a)
 #pragma unroll
     for (int c = 0; c < 2; ++c) acc[a][c] = (f64x4){0.0, 0.0, 0.0, 0.0};
-  for (int kk = 0; kk < kHeadDim; kk += kSK) {
+  for (int kk = 0; kk < kHeadDim; kk += SK) {
     __syncthreads();   // the previous chunk is no longer read
 #pragma unroll
-    for (int d = 0; d < 4; ++d) {
+    for (int d = 0; d < kD; ++d) {
       qs[sd0 + d][sr] = qv[d];
       ks[sd0 + d][sr] = kv[d];
     }
     __syncthreads();
-    if (kk + kSK < kHeadDim) {
+    if (kk + SK < kHeadDim) {
 #pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        qv[d] = qin ? qrow[kk + kSK + d] : 0.0;
-        kv[d] = kin ? krow[kk + kSK + d] : 0.0;
+      for (int d = 0; d < kD; ++d) {
+        qv[d] = qin ? qrow[kk + SK + d] : 0.0;
+        kv[d] = kin ? krow[kk + SK + d] : 0.0;
       }
     }
-    // a wave whose 64 rows or 32 columns all lie past the matrix edge only
+    // a wave whose rows or columns all lie past the matrix edge only
     // helps stage the operands.  A[i][k]: lane holds row i = li of the tile,
     // k = lk; B[k][j]: column j = li.  The fragments of the next k-step are
     // read while this step's 8 products run.
     if (wave_live) {
-      double af[2][4], bf[2][2];
+      double af[2][TA], bf[2][2];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) af[0][t] = qs[lk][wr * 64 + t * 16 + li];
+      for (int t = 0; t < TA; ++t) af[0][t] = qs[lk][wr * kWaveRows + t * 16 + li];
 #pragma unroll
       for (int t = 0; t < 2; ++t) bf[0][t] = ks[lk][wc * 32 + t * 16 + li];
 #pragma unroll
-      for (int k4 = 0; k4 < kSK; k4 += 4) {
+      for (int k4 = 0; k4 < SK; k4 += 4) {
         const int cur = (k4 / 4) & 1;
-        if (k4 + 4 < kSK) {
+        if (k4 + 4 < SK) {
 #pragma unroll
-          for (int t = 0; t < 4; ++t) af[cur ^ 1][t] = qs[k4 + 4 + lk][wr * 64 + t * 16 + li];
+          for (int t = 0; t < TA; ++t) af[cur ^ 1][t] = qs[k4 + 4 + lk][wr * kWaveRows + t * 16 + li];
 #pragma unroll
           for (int t = 0; t < 2; ++t) bf[cur ^ 1][t] = ks[k4 + 4 + lk][wc * 32 + t * 16 + li];
         }
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+        for (int a = 0; a < TA; ++a)
 #pragma unroll
           for (int c = 0; c < 2; ++c)
             acc[a][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[cur][a], bf[cur][c], acc[a][c], 0, 0, 0);
@@ -260,11 +269,11 @@ __global__ __launch_bounds__(512) void score_kernel(const double* __restrict__ q
     }
   }
   // D tile element (4 r + lane / 16, lane % 16) sits in register r of the lane
-  if (i0 + kST <= n && j0 + kST <= nk && !scores32) {
+  if (i0 + ST <= n && j0 + ST <= nk && !scores32) {
     // interior tile, float64 scores only: no per-element checks
-    double* out = scores + ((int64_t)bh * n + i0 + wr * 64 + lk) * nk + j0 + wc * 32 + li;
+    double* out = scores + ((int64_t)bh * n + i0 + wr * kWaveRows + lk) * nk + j0 + wc * 32 + li;
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < TA; ++a)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -272,10 +281,10 @@ __global__ __launch_bounds__(512) void score_kernel(const double* __restrict__ q
     return;
   }
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < TA; ++a)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int i = i0 + wr * 64 + a * 16 + 4 * r + lk;
+      const int i = i0 + wr * kWaveRows + a * 16 + 4 * r + lk;
       if (i >= n) continue;
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
@@ -1378,12 +1387,26 @@ hipError_t launch_select(const void* in, int64_t rows, int n, double top_p, int 
 }
 }  // namespace
 
+namespace {
+template <int ST, int SK, int WR, int TA>
+void launch_score(const double* qbar, const double* kbar, int BH, int n, int nk, double sm_scale, double* scores,
+                  float* block_scores, hipStream_t st) {
+  hipLaunchKernelGGL((score_kernel<ST, SK, WR, TA>), dim3((nk + ST - 1) / ST, (n + ST - 1) / ST, BH), dim3(4 * ST), 0,
+                     st, qbar, kbar, n, nk, sm_scale, scores, block_scores);
+}
+}  // namespace
+
 hipError_t launch_score_select(const double* qbar, const double* kbar, int B, int H, int n, int nk,
                                double sm_scale, double top_p, int k_min, double* scores, int32_t* counts,
                                uint32_t* bitmap, int words, float* block_scores, hipStream_t st) {
-  const int tiles_q = (n + kST - 1) / kST, tiles_k = (nk + kST - 1) / kST;
-  hipLaunchKernelGGL(score_kernel, dim3(tiles_k, tiles_q, B * H), dim3(512), 0, st, qbar, kbar, n, nk, sm_scale,
-                     scores, block_scores);
+  const int64_t tiles64 = (int64_t)((n + 63) / 64) * ((nk + 63) / 64) * B * H;
+  // Tiles of 32 while those of 64 would use well under half the 256 CUs (74
+  // blocks x 24 heads, 96 tiles: 7.2 against 9.8 us; 317 x 5, 125 tiles: 11.8
+  // against 10.7; 128 x 40, 160 tiles: 14.0 against 10.3).
+  if (tiles64 <= 96)
+    launch_score<32, 64, 2, 1>(qbar, kbar, B * H, n, nk, sm_scale, scores, block_scores, st);
+  else
+    launch_score<64, 16, 2, 2>(qbar, kbar, B * H, n, nk, sm_scale, scores, block_scores, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_select<false>(scores, (int64_t)B * H * n, nk, top_p, k_min, counts, bitmap, words, st);

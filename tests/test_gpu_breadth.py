@@ -122,3 +122,29 @@ def test_full_size_f16_builder_and_attention(key):
                 o_ref, _ = oa.attention_block(qh, kh, vh, oa.row_blocks(rp, ci, r), i, wl.sm_scale)
                 worst = max(worst, _max_err(oh[i * 64:i * 64 + o_ref.shape[0]], o_ref))
     assert worst <= 2e-3, worst
+
+
+@pytest.mark.parametrize("kv_block", [64, 128])
+@pytest.mark.parametrize("n,H", [(1, 1), (31, 2), (32, 2), (33, 3), (65, 5), (64, 96), (64, 97), (65, 25), (97, 30), (129, 12)])
+def test_block_scores_at_the_edges_of_their_tiles(n, H, kv_block):
+    """Tiles of 32 (small launches) and of 64: sizes that end inside, at and
+    past a tile and on both sides of the rule, against float64 block means and
+    products.  The fp32 copy rounds once: 2^-24 of the value, plus the float64
+    sums' own 1e-12."""
+    S = 64 * n - 5
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    q, k = (torch.randn(1, S, H, 128, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    m = ops.build_block_mask(q, k, 0.5, 0.1, return_scores=True, kv_block=kv_block)
+
+    def means(x, block):
+        nb = -(-S // block)
+        y = torch.zeros(nb * block, H, 128, dtype=torch.float64, device="cuda")
+        y[:S] = x[0]
+        cnt = torch.full((nb, 1, 1), float(block), dtype=torch.float64, device="cuda")
+        cnt[-1] = S - (nb - 1) * block
+        return y.reshape(nb, block, H, 128).sum(1) / cnt
+
+    qm, km = means(q, 64), means(k, kv_block)
+    ref = torch.stack([qm[:, h] @ km[:, h].t() for h in range(H)]).reshape(H * n, -1) / math.sqrt(128)
+    err = (m.block_scores.double() - ref).abs()
+    assert bool((err <= 2.0 ** -24 * ref.abs() + 1e-12).all()), float(err.max())
