@@ -88,23 +88,6 @@ inline unsigned work_grid(int U, int np) {
 constexpr int kRotDiv = 192;
 __device__ inline int walk_target(int i, int n) { return (int)((int64_t)i * n / kRotDiv % n); }
 
-// Offset in [0, p1 - p0) of the first position p of [p0, p1) whose id(p)
-// reaches `target` (ids ascending), 0 when none does: the rotation of the
-// walk over [p0, p1).  Any other id order still gives a rotation, so every
-// position is visited once whatever the row holds.
-template <class F>
-__device__ inline int walk_rotation(int p0, int p1, int target, F id) {
-  int lo = p0, hi = p1;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (id(mid) < target)
-      lo = mid + 1;
-    else
-      hi = mid;
-  }
-  return lo == p1 ? 0 : lo - p0;
-}
-
 // One global -> LDS direct load (16 bytes per lane, lane-linear destination
 // at `lds`, a wave-uniform LDS byte address).  The LDS address travels in
 // m0; the statement saves m0 to a scratch SGPR, sets it, waits the one wait
@@ -151,8 +134,11 @@ __device__ inline void dma16x4(uint32_t lds, const void* sbase, const uint32_t (
       : "memory", "scc");
 }
 
-// walk_rotation over ascending ids, counted by the whole wave: the list is
-// read in coalesced runs instead of by dependent scalar loads.
+// Offset in [0, p1 - p0) of the first position of [p0, p1) whose id reaches
+// `target` (ids ascending), 0 when none does: the rotation of the walk over
+// [p0, p1).  It is the number of ids below the target, counted by the whole
+// wave, so the list is read in coalesced runs.  Any other id order still gives
+// a rotation, so every position is visited once whatever the row holds.
 template <bool KV2>
 __device__ inline int walk_rotation_wave(const int32_t* col, int p0, int p1, int target) {
   int below = 0;
@@ -192,6 +178,7 @@ struct PairWalk {
   int b0, lb, rb, cb;
   int n, target;
   bool dense;
+  // The two lists' bounds; the caller sets the rotations ra and rb.
   __device__ void init(const AttnArgs& a, bool is_dense, int b, int h, int ip) {
     col = as_constant(a.col_idx);
     n = a.n;
@@ -217,9 +204,7 @@ struct PairWalk {
         lb *= 2;
       }
     }
-    auto id = [&](int p) { return id_at(p); };
-    ra = walk_rotation(a0, a0 + la, target, id);
-    rb = walk_rotation(b0, b0 + lb, target, id);
+    ra = rb = 0;
     ca = cb = 0;
   }
   __device__ bool listed(int sel) const { return sel == 0 ? la > 0 : lb > 0; }

@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import attention as oa
 from oracle import fp8 as of
 from oracle import guidance as og
 from oracle import mask as om
@@ -148,3 +149,27 @@ def test_block_scores_at_the_edges_of_their_tiles(n, H, kv_block):
     ref = torch.stack([qm[:, h] @ km[:, h].t() for h in range(H)]).reshape(H * n, -1) / math.sqrt(128)
     err = (m.block_scores.double() - ref).abs()
     assert bool((err <= 2.0 ** -24 * ref.abs() + 1e-12).all()), float(err.max())
+
+
+@pytest.mark.parametrize("kv_block", [64, 128])
+@pytest.mark.parametrize("keep", [0.03, 0.5, 0.97])
+def test_fp8_walk_start_over_short_and_long_lists(keep, kv_block):
+    """The start of a pair's walk is counted 256 ids at a time: pairs with no,
+    few and more than 256 ids, and ids outside [0, n_kv), against the oracle."""
+    S, n = 64 * 141 - 7, 141
+    nk = -(-S // kv_block)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    quant = [ops.quantize_fp8_blockwise(torch.randn(1, S, 1, 128, generator=gen, device="cuda").to(torch.bfloat16))
+             for _ in range(3)]
+    rp, ci = wk.random_csr(np.random.Generator(np.random.PCG64(3)), n, nk, keep, empty_frac=0.1)
+    rows = [np.concatenate([[-1], ci[rp[r]:rp[r + 1]], [nk]]) if r % 4 == 3 else ci[rp[r]:rp[r + 1]] for r in range(n)]
+    mask = ops.BlockMask.from_host(np.concatenate([[0], np.cumsum([len(x) for x in rows])]), np.concatenate(rows), 1, 1,
+                                   n, block=kv_block)
+    out = ops.block_sparse_attn_fwd(*(c for c, _ in quant), mask, scales=tuple(s for _, s in quant))
+    dq, dk, dv = (of.dequantize_blockwise(c.cpu().numpy(), s.cpu().numpy()) for c, s in quant)
+    O, _ = oa.attention(dq, dk, dv, rp, ci, 1.0 / math.sqrt(128), 1, kv_block=kv_block)
+    A, _ = oa.attention(dq, dk, np.abs(dv), rp, ci, 1.0 / math.sqrt(128), 1, kv_block=kv_block)
+    # a probability rounds to e4m3 within 2^-4 of itself (2e-3 covers those below its
+    # normal range), the output to bf16
+    err = np.abs(out.float().cpu().numpy() - O)
+    assert np.all(err <= 2.0 ** -4 * A + 2.0 ** -8 * np.abs(O) + 2e-3), float(err.max())
