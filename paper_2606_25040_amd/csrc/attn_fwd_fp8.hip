@@ -141,7 +141,7 @@ void attn_fwd_fp8_kernel(AttnArgs a, int np) {
   // binary search per list was a chain of dependent scalar loads ahead of the
   // first tile.  With Q requested first and the V scales read behind the
   // first tiles: 13 x 30 x 52 x 24 heads at 12 % (kv blocks of 128) 7 us of
-  // 565, 720p 14B 7.43 against 7.45 ms.
+  // 565; 720p 14B, with 31 rounds of long walks, within the runs' spread.
   if (!DENSE) {
     int below_a = 0, below_b = 0;
     const int la = walk.la, lt = walk.la + walk.lb;
