@@ -46,6 +46,8 @@
 // and walks each as its two 64-token halves.  Each flag is its own
 // instantiation, so the plain path carries none of the others' work.
 // Without a mask attn_dense_16_kernel below runs, except on small launches.
+#include <cfloat>
+
 #include "attn_common.h"
 
 namespace chorus {
@@ -240,7 +242,10 @@ void attn_fwd_16_kernel(AttnArgs a) {
   const int v_sl = v_swz_bits(j16 >> 2);
 
   const float cl2 = a.sm_scale * kLog2e;
-  float m_run = -INFINITY, l_run = 0.f, rs = 0.f;
+  // The running max of parts 1 .. P - 1 starts at the lowest finite value: a
+  // part may begin with a block whose logits are all -inf (keys masked through
+  // K), and -inf - (-inf) is NaN.  Part 0 begins where the unsplit walk does.
+  float m_run = P > 1 && part > 0 ? -FLT_MAX : -INFINITY, l_run = 0.f, rs = 0.f;
   f32x16 o[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u)
@@ -402,8 +407,9 @@ void attn_fwd_16_kernel(AttnArgs a) {
     float m_all = m_run;
 #pragma unroll
     for (int x = 1; x < P; ++x) m_all = fmaxf(m_all, ml[x][wave][0][l32]);
-    // a part without blocks has m = -inf and nothing to add
-    auto weight = [&](float m) { return m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - m_all); };
+    // m_all is finite or +inf: a part that saw no finite logit gets weight 0,
+    // or has nothing to add
+    auto weight = [&](float m) { return __builtin_amdgcn_exp2f(m - m_all); };
     const float f0 = weight(m_run);
     l_tot *= f0;
 #pragma unroll

@@ -336,6 +336,44 @@ def test_attention_in_list_parts_matches_oracle(dtype, kv_block, key_scale, H, S
         assert np.max(np.abs(got[fin] - L[fin])) <= 1e-3
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("kv_block", [64, 128])
+@pytest.mark.parametrize("masked", [True, False])
+@pytest.mark.parametrize("H", [2, 20, 40])
+def test_keys_masked_through_k_weigh_nothing(dtype, kv_block, masked, H):
+    """Keys whose logits are -inf for every query (one element of K at -inf, of
+    Q at 1) weigh nothing wherever their blocks lie in a row's list, as long as
+    the walk does not begin with them: whole blocks in the middle and at the
+    end, so that the parts of a split list (H = 2 and 20) begin with them and
+    the unsplit walk (H = 40) passes over them.  Reference: float64 softmax
+    with those keys left out."""
+    gen = torch.Generator().manual_seed(H)
+    S = 64 * 14 - 9
+    q, k, v = (x.cuda() for x in rand_qkv(gen, 1, S, H, dtype))
+    n, nk = 14, -(-S // kv_block)
+    dead = torch.zeros(S, dtype=torch.bool, device="cuda")
+    dead[128 * 2:128 * 4] = True
+    dead[128 * 5:] = True
+    q[..., 0] = 1.0
+    k[:, dead, :, 0] = -math.inf
+    keep = torch.ones(n, nk, dtype=torch.bool)
+    if masked:
+        keep[:, 1::2] = torch.rand(n, nk // 2, generator=gen) < 0.7
+    mask = None
+    if masked or kv_block == 128:
+        rows = keep.repeat(H, 1)
+        mask = ops.BlockMask.from_host(np.concatenate([[0], np.cumsum(rows.sum(1).numpy())]), rows.nonzero()[:, 1].numpy(),
+                                       1, H, n, block=kv_block)
+    out, lse = ops.block_sparse_attn_fwd(q, k, v, mask, return_lse=True)
+    live = keep.cuda().repeat_interleave(64, 0)[:S].repeat_interleave(kv_block, 1)[:, :S] & ~dead
+    for h in (0, H - 1):
+        kk = k[0, :, h].double().masked_fill(dead[:, None], 0.0)
+        s = (q[0, :, h].double() @ kk.t() / math.sqrt(128)).masked_fill(~live, -math.inf)
+        O = torch.softmax(s, 1) @ v[0, :, h].double()
+        assert within_rounding(np64(out[0, :, h]), O.cpu().numpy(), dtype)
+        assert float((lse[0, h].double() - torch.logsumexp(s, 1)).abs().max()) <= 1e-3
+
+
 def test_attention_strided_views_and_determinism():
     gen = torch.Generator().manual_seed(9)
     B, S, H = 2, 500, 2
