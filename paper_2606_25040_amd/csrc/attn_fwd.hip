@@ -38,8 +38,8 @@
 // global addresses instead of the LDS ones) so that the b128 K reads and the
 // transposed b64 V reads are bank-conflict free.
 // Epilogue: O = O^T / l written as 16-bit, lse = ln(sum exp) in fp32.
-// With P > 1 a workgroup of P wave pairs splits the row's walk into P runs, each
-// with tiles of its own, and part 0 merges the (m, l, O) of the others at the
+// With P > 1 a workgroup of P wave pairs splits the row's walk into up to P runs,
+// each with tiles of its own, and part 0 merges the (m, l, O) of the others at the
 // end: for launches with too few rows to fill the chip (list_parts).
 // Template flags: DENSE walks every kv block; KSCALE multiplies the logits of keys below n_first by beta
 // (first-frame key enhancement, Eq. 1); KV2 reads a mask of 128-token kv blocks
@@ -139,6 +139,12 @@ struct HalfLoader {
   }
 };
 
+// Listed blocks from which a row is split in two and in four parts.  The merge
+// costs about 1 us of a row's latency, a block 0.75 us unsplit: a list of 3
+// takes 9.0 us unsplit and 9.2 in two parts, one of 5 11.2 and 10.4; one of 12
+// 14.2 in two and 14.8 in four, one of 20 19.4 and 18.8.
+constexpr int kSplit2 = 4, kSplit4 = 16;
+
 template <bool BF16, bool DENSE, bool KSCALE, bool KV2, int P>
 __global__ __launch_bounds__(128 * P) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_fwd_16_kernel(AttnArgs a) {
@@ -174,11 +180,16 @@ void attn_fwd_16_kernel(AttnArgs a) {
   const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wave = wave_id & 1, part = wave_id >> 1;   // query half, share of the list
   const int L = kb1 - kb0;
+  // Short lists use fewer parts than the launch brings; the waves of the others
+  // leave here, ahead of every barrier.
+  const int parts = P == 1 ? 1 : L < kSplit2 ? 1 : P == 2 || L < kSplit4 ? 2 : 4;
+  if (P > 1 && part >= parts) return;
   int left = L, pos = kb0;
   if (!DENSE && L > 0) pos += walk_rotation_wave<KV2>(a.col_idx, kb0, kb1, walk_target(i, n));
   if (P > 1) {   // this part's run of the walk
-    const int w0 = (int)((int64_t)part * L / P);
-    left = (int)((int64_t)(part + 1) * L / P) - w0;
+    const int lp = parts >> 1;   // log2(parts)
+    const int w0 = (int)((int64_t)part * L >> lp);
+    left = (int)((int64_t)(part + 1) * L >> lp) - w0;
     pos += w0;
     if (pos >= kb1) pos -= L;
   }
@@ -374,7 +385,7 @@ void attn_fwd_16_kernel(AttnArgs a) {
       step(s1, s0);
     }
   } else {
-    const int steps = (L + P - 1) / P;   // of the longest part
+    const int steps = (L + parts - 1) >> (parts >> 1);   // of the longest part
     for (int x = 0; x < steps; ++x) {
       step(s0, s1);
       if (++x >= steps) break;
@@ -383,8 +394,8 @@ void attn_fwd_16_kernel(AttnArgs a) {
   }
 
   float l_tot = pair_sum(l_run);   // lane pair (l, l ^ 32) holds partial sums of the same query
-  if (P > 1) {
-    // Parts 1 .. P - 1 hand their (m, l, O) to part 0 through the tiles.
+  if (P > 1 && parts > 1) {
+    // Parts 1 .. parts - 1 hand their (m, l, O) to part 0 through the tiles.
     float* mine = reinterpret_cast<float*>(&kv_s[part][0][0]);
     __shared__ float ml[P][2][2][32];   // [part][query half][m, l][query]
     CHORUS_WAIT_LDS_TILES();
@@ -406,7 +417,8 @@ void attn_fwd_16_kernel(AttnArgs a) {
     if (part > 0) return;
     float m_all = m_run;
 #pragma unroll
-    for (int x = 1; x < P; ++x) m_all = fmaxf(m_all, ml[x][wave][0][l32]);
+    for (int x = 1; x < P; ++x)
+      if (x < parts) m_all = fmaxf(m_all, ml[x][wave][0][l32]);
     // m_all is finite or +inf: a part that saw no finite logit gets weight 0,
     // or has nothing to add
     auto weight = [&](float m) { return __builtin_amdgcn_exp2f(m - m_all); };
@@ -418,6 +430,7 @@ void attn_fwd_16_kernel(AttnArgs a) {
       for (int r = 0; r < 16; ++r) o[u][r] *= f0;
 #pragma unroll
     for (int x = 1; x < P; ++x) {
+      if (x >= parts) break;
       const float f = weight(ml[x][wave][0][l32]);
       l_tot += f * ml[x][wave][1][l32];
       const float4* their = reinterpret_cast<const float4*>(&kv_s[x][0][0]);
@@ -721,18 +734,22 @@ void launch_16(const AttnArgs& a, hipStream_t st) {
     hipLaunchKernelGGL((attn_fwd_16_kernel<BF16, DENSE, false, KV2, P>), grid, block, 0, st, a);
 }
 
-// Parts a row's list is split into.  A workgroup with P parts takes P times the
-// LDS, so a CU holds four (P = 1), two or one of them; a split pays while the
-// rows alone leave that room empty.  One row per CU or fewer: four parts
-// (4,096 tokens, 2 heads, f16: 22 us, unsplit 35); two per CU or fewer: two
-// (3,900 tokens, 5 heads: 27 us, four parts 37, unsplit 38).  Beyond that the
-// rows fill the chip (3,900 tokens, 10 heads: 42 us either way).  Dense calls
+// Parts a row's list is split into, at most (short lists use fewer, kSplit2
+// and kSplit4).  A workgroup with P parts takes P times the LDS, so a CU holds
+// four (P = 1), two or one of them; a split pays while the rows alone leave
+// that room empty.  Rows are dealt to the XCDs by whole (request, head) units,
+// so what counts is the fullest XCD's share against its 32 CUs.  One row per CU
+// or fewer: four parts (4,096 tokens, 2 heads, all blocks listed: 41 us, two
+// parts 48, unsplit 78).  Two per CU or fewer: two parts (12 heads x 20 blocks,
+// 40 rows on XCDs 0..3: 27 us, unsplit 37, four parts 35).  Beyond that the rows
+// fill the chip (12 heads x 42 blocks, 84 rows: 85 us, unsplit 77).  Dense calls
 // of that size run here too, 3,120 tokens x 4 heads: 35 us against 53 with
 // attn_dense_16_kernel.  The rule reads sizes only, so a full mask and no mask
 // take the same split.
 int list_parts(const AttnArgs& a) {
-  const int64_t rows = (int64_t)a.B * a.H * a.n;
-  return rows <= 256 ? 4 : rows <= 512 ? 2 : 1;
+  if (a.n < kSplit2) return 1;
+  const unsigned rows = work_grid(a.B * a.H, a.n) / kNumXcd;
+  return rows <= 32 ? 4 : rows <= 64 ? 2 : 1;
 }
 
 template <bool BF16, int NW>

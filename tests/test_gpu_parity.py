@@ -310,7 +310,7 @@ def test_dense_kernel_variants_are_bitwise_the_full_mask(dtype, B, S, H):
 @pytest.mark.parametrize("key_scale", [None, (700, 1.5)])
 @pytest.mark.parametrize("H,S", [(16, 1000), (17, 960), (32, 1000), (33, 960), (40, 970)])
 def test_attention_in_list_parts_matches_oracle(dtype, kv_block, key_scale, H, S):
-    """Rows split into four (up to 256 rows), two (up to 512) or no parts: rows
+    """Launches whose rows split into four, two or no parts: rows
     shorter than the number of parts, empty rows, ids outside [0, n_kv) and a
     missing second half at the end, first and last head against the oracle."""
     gen = torch.Generator().manual_seed(H)
@@ -336,24 +336,51 @@ def test_attention_in_list_parts_matches_oracle(dtype, kv_block, key_scale, H, S
         assert np.max(np.abs(got[fin] - L[fin])) <= 1e-3
 
 
+@pytest.mark.parametrize("kv_block", [64, 128])
+@pytest.mark.parametrize("H,n", [(1, 3), (2, 22), (8, 32), (9, 16), (9, 17), (17, 21), (17, 22)])
+def test_rows_of_every_length_in_list_parts(kv_block, H, n):
+    """The most parts follow the fullest XCD's rows (up to 32: four, up to 64:
+    two, whole heads to an XCD: 9 heads x 16 and 17, 17 x 21 and 22 blocks lie on
+    both sides), a row's parts its length: 0 to all blocks, so lists of 3, 4, 15
+    and 16 steps and a missing second half at the end, against the oracle."""
+    gen = torch.Generator().manual_seed(n)
+    S = 64 * n - 17
+    q, k, v = rand_qkv(gen, 1, S, H, torch.bfloat16)
+    nk = -(-S // kv_block)
+    rng = np.random.Generator(np.random.PCG64(H))
+    rows = [np.sort(rng.choice(nk, (r + r // n) % (nk + 1), replace=False)) for r in range(H * n)]
+    rp, ci = np.concatenate([[0], np.cumsum([len(x) for x in rows])]), np.concatenate(rows)
+    mask = ops.BlockMask.from_host(rp, ci, 1, H, n, block=kv_block)
+    out, lse = ops.block_sparse_attn_fwd(q.cuda(), k.cuda(), v.cuda(), mask, return_lse=True)
+    for h in sorted({0, H // 2, H - 1}):
+        a, b = rp[h * n], rp[(h + 1) * n]
+        O, L = oa.attention(*(np64(x[:, :, h:h + 1]) for x in (q, k, v)), rp[h * n:(h + 1) * n + 1] - a, ci[a:b],
+                            1.0 / math.sqrt(128), 1, kv_block=kv_block)
+        assert within_rounding(np64(out[:, :, h:h + 1]), O, torch.bfloat16, atol=TOL16)
+        got = lse[:, h:h + 1].cpu().numpy()
+        assert np.array_equal(np.isfinite(got), np.isfinite(L))
+        fin = np.isfinite(L)
+        assert np.max(np.abs(got[fin] - L[fin])) <= 1e-3
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 @pytest.mark.parametrize("kv_block", [64, 128])
 @pytest.mark.parametrize("masked", [True, False])
-@pytest.mark.parametrize("H", [2, 20, 40])
-def test_keys_masked_through_k_weigh_nothing(dtype, kv_block, masked, H):
+@pytest.mark.parametrize("H,n", [(2, 30), (20, 14), (40, 14)])
+def test_keys_masked_through_k_weigh_nothing(dtype, kv_block, masked, H, n):
     """Keys whose logits are -inf for every query (one element of K at -inf, of
     Q at 1) weigh nothing wherever their blocks lie in a row's list, as long as
     the walk does not begin with them: whole blocks in the middle and at the
-    end, so that the parts of a split list (H = 2 and 20) begin with them and
-    the unsplit walk (H = 40) passes over them.  Reference: float64 softmax
+    end, so that the parts of a split list (two heads: four, 20: two) begin with
+    them and the unsplit walk (40) passes over them.  Reference: float64 softmax
     with those keys left out."""
     gen = torch.Generator().manual_seed(H)
-    S = 64 * 14 - 9
+    S = 64 * n - 9
     q, k, v = (x.cuda() for x in rand_qkv(gen, 1, S, H, dtype))
-    n, nk = 14, -(-S // kv_block)
+    nk = -(-S // kv_block)
     dead = torch.zeros(S, dtype=torch.bool, device="cuda")
-    dead[128 * 2:128 * 4] = True
-    dead[128 * 5:] = True
+    for a, b in ((2, 4), (5, 7)) if n == 14 else ((5, 8), (11, 15)):   # no row's walk starts there
+        dead[128 * a:128 * b] = True
     q[..., 0] = 1.0
     k[:, dead, :, 0] = -math.inf
     keep = torch.ones(n, nk, dtype=torch.bool)
