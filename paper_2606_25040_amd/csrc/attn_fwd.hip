@@ -45,7 +45,8 @@
 // (first-frame key enhancement, Eq. 1); KV2 reads a mask of 128-token kv blocks
 // and walks each as its two 64-token halves.  Each flag is its own
 // instantiation, so the plain path carries none of the others' work.
-// Without a mask attn_dense_16_kernel below runs, except on small launches.
+// Without a mask attn_dense_16_kernel below runs, except on small launches
+// (launch_dense).
 #include <cfloat>
 
 #include "attn_common.h"
@@ -762,16 +763,26 @@ void launch_dense_nw(const AttnArgs& a, hipStream_t st) {
     hipLaunchKernelGGL((attn_dense_16_kernel<BF16, false, NW>), grid, block, 0, st, a, np);
 }
 
-// Waves per workgroup of the dense kernel: more waves share a tile, fewer
-// leave smaller pieces for the CUs (each CU holds eight such waves).  With
-// four rounds of eight-wave workgroups over the 256 CUs the sharing wins (480p
-// 14B: 17.9 against 19.0 ms); below that the uneven last round costs more
-// (S = 8,215, 3 heads: 0.204 ms with eight waves, 0.164 with four).  Two waves
-// were slower even there (0.236 ms).
+// Dense calls whose rows are not split.  The masked kernel's workgroups (two
+// waves) while the dense kernel's larger ones fill the chip worse than its
+// pipeline gains: below 4 kv blocks (1,000 heads x 3 blocks 47-51 us against 54)
+// and, for short sequences, up to 96 rows on the fullest XCD (80 heads x 9
+// blocks 26.6 against 27.7, 128 x 5 18.0 against 19.1, 24 x 28 56.8 against
+// 56.5).  Otherwise the dense kernel: more waves share a tile, fewer leave
+// smaller pieces for the CUs (each CU holds eight such waves).  With long
+// sequences and four rounds of eight-wave workgroups over the 256 CUs the
+// sharing wins (480p 14B: 17.9 against 19.0 ms; 256 heads x 32 blocks 565
+// against 597 us); below that the uneven last round costs more (S = 8,215, 3
+// heads: 0.204 ms with eight waves, 0.164 with four), and on short sequences the
+// waves past the end (1,000 heads x 5 blocks: 154 us against 111, x 13 520
+// against 462).  Two waves were slower even there (0.236 ms).
 template <bool BF16>
 void launch_dense(const AttnArgs& a, hipStream_t st) {
+  const unsigned rows = work_grid(a.B * a.H, a.n) / kNumXcd;
   const int64_t rows32 = (int64_t)a.B * a.H * ((a.S + 31) / 32);
-  if (rows32 >= 4 * 256 * 8)
+  if (a.n < 4 || (a.n < 32 && rows <= 96))
+    launch_16<BF16, true, false, 1>(a, st);
+  else if (a.n >= 64 && rows32 >= 4 * 256 * 8)
     launch_dense_nw<BF16, 8>(a, st);
   else
     launch_dense_nw<BF16, 4>(a, st);

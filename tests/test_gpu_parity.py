@@ -336,6 +336,36 @@ def test_attention_in_list_parts_matches_oracle(dtype, kv_block, key_scale, H, S
         assert np.max(np.abs(got[fin] - L[fin])) <= 1e-3
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("B,S,H", [(1, 189, 600), (1, 250, 200), (2, 850, 20), (1, 1950, 40), (1, 4150, 8), (2, 4150, 32)])
+def test_dense_over_growing_logits_matches_oracle(dtype, B, S, H):
+    """No mask, with rows not split: the masked kernel's workgroups (3, 4 and 14
+    kv blocks), four waves (31 and 65) and eight (65, 64 heads), on slices of one
+    packed QKV tensor.  The row maxima rise by 2^80 over the first 60 % of the
+    walk and fall after it, so O and l are rescaled along the way.  First and
+    last (request, head) against the oracle; P rounds to the type, so the bound
+    carries one rounding of sum(p |v|)."""
+    gen = torch.Generator(device="cuda").manual_seed(S)
+    qkv = torch.randn(B, S, 3, H, 128, generator=gen, device="cuda") * 0.5
+    qkv[:, :, 0, :, 0] = 4.0
+    t = torch.arange(S, device="cuda") / S
+    qkv[:, :, 1, :, 0] += (160 * torch.minimum(t / 0.6, 1 - (t - 0.6)))[None, :, None]
+    qkv = qkv.to(dtype)
+    q, k, v = qkv[:, :, 0], qkv[:, :, 1], qkv[:, :, 2]
+    n = (S + 63) // 64
+    for key_scale in (None, (S // 3, 1.25)):
+        out, lse = ops.block_sparse_attn_fwd(q, k, v, None, return_lse=True, key_scale=key_scale)
+        for b, h in ((0, 0), (B - 1, H - 1)):
+            qq, kk, vv = (np64(x[b:b + 1, :, h:h + 1]).astype(np.float64) for x in (q, k, v))
+            if key_scale is not None:
+                kk = og.enhance_first_frame_keys(kk, *key_scale)
+            rp, ci = np.arange(n + 1) * n, np.tile(np.arange(n), n)
+            O, L = oa.attention(qq, kk, vv, rp, ci, 1.0 / math.sqrt(128), 1)
+            A, _ = oa.attention(qq, kk, np.abs(vv), rp, ci, 1.0 / math.sqrt(128), 1)
+            assert within_rounding(np64(out[b:b + 1, :, h:h + 1]), O, dtype, ref_abs=A)
+            assert np.max(np.abs(lse[b:b + 1, h:h + 1].cpu().numpy() - L)) <= 1e-3
+
+
 @pytest.mark.parametrize("kv_block", [64, 128])
 @pytest.mark.parametrize("H,n", [(1, 3), (2, 22), (8, 32), (9, 16), (9, 17), (17, 21), (17, 22)])
 def test_rows_of_every_length_in_list_parts(kv_block, H, n):
