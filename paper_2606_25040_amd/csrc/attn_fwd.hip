@@ -30,7 +30,7 @@
 // ran QK^T, softmax and PV of a 64-key block one after the other on single
 // buffers, and faster: batch-4 480p 14B (bf16, 15 %) 14.09 against 15.00 ms,
 // 720p 5B (bf16, 20 %) 2.00 against 2.10 ms, f16 with kv blocks of 128 and a
-// key scale (2 x 16 heads, S = 17,523) 1.22 against 1.26 ms.  Measured beside
+// key scale (2 x 16 heads, S = 17,523) 1.20 against 1.26 ms.  Measured beside
 // it: two q-blocks per workgroup walking the union of their lists 15.8 ms
 // (every fifth step has work for one of them only), separate waits for K and V
 // 15.60 against 15.17 ms, raised wave priority during QK^T 15.39.
@@ -371,8 +371,8 @@ void attn_fwd_16_kernel(AttnArgs a) {
       pv(pf, v_s[1]);
       l_run += rs;
       mx = row_max(sn);
-      if (jn >= 0 && (KSCALE || jn * kBlock + kBlock > S)) {
-        fix(sn, jn);
+      if (jn >= 0 && ((KSCALE && jn * kBlock < a.ks.n_first) || jn * kBlock + kBlock > S)) {
+        fix(sn, jn);   // rare: first-frame blocks and a partial last one take the maximum again
         mx = row_max(sn);
       }
     }
