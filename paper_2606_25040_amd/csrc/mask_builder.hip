@@ -182,9 +182,10 @@ __global__ __launch_bounds__(kHeadDim) void means_from_sums_kernel(const double*
 // multiplied.  Writes float64 scores into the workspace and, optionally, fp32
 // copies.  An element is the same chain of products whatever the tile, so the
 // scores are the same bits.
-// What bounds it: the fp64 matrix rate (64 cycles per MFMA), so a tile of 128
-// keeps one CU busy for 22 us however small the launch, and its padding and
-// uneven last round count.  Tiles of 64 (SK 16) against 128: 74 blocks x 12
+// What bounds it: the fp64 matrix rate.  The products of a tile of 128 take one
+// CU 13.7 us (2,048 MFMAs of 64 cycles on four SIMDs at 2.4 GHz), with staging
+// and the store 22 to 24 measured, however small the launch, and its padding
+// and uneven last round count.  Tiles of 64 (SK 16) against 128: 74 blocks x 12
 // heads 11.0 against 24.3 us, 317 x 24 22.3 against 28.6, 512 x 40 63.6
 // against 72.2, 1,182 x 40 293 against 318.  The staging writes conflict in
 // LDS when SK grows (SK 32: 91 us at 512 x 40); row paddings of 4 or 16
@@ -1399,11 +1400,13 @@ void launch_score(const double* qbar, const double* kbar, int BH, int n, int nk,
 hipError_t launch_score_select(const double* qbar, const double* kbar, int B, int H, int n, int nk,
                                double sm_scale, double top_p, int k_min, double* scores, int32_t* counts,
                                uint32_t* bitmap, int words, float* block_scores, hipStream_t st) {
-  const int64_t tiles64 = (int64_t)((n + 63) / 64) * ((nk + 63) / 64) * B * H;
-  // Tiles of 32 while those of 64 would use well under half the 256 CUs (74
-  // blocks x 24 heads, 96 tiles: 7.2 against 9.8 us; 317 x 5, 125 tiles: 11.8
-  // against 10.7; 128 x 40, 160 tiles: 14.0 against 10.3).
-  if (tiles64 <= 96)
+  // Tiles of 32 while there is at most one per CU: more tiles for the CUs and
+  // less padding.  Builder times with 32 against 64: 2 heads x 74 blocks 23.3
+  // and 24.3 us, 160 x 14 35.2 and 37.4; beyond the line 12 x 160 (300 tiles of
+  // 32) 44.0 and 37.0, 80 x 42 (320) 51.2 and 44.3.  At it they are close: 64 x
+  // 64 (256) 53.2 and 51.8, 5 x 200 (245) 32.5 and 30.9.
+  const int64_t tiles32 = (int64_t)((n + 31) / 32) * ((nk + 31) / 32) * B * H;
+  if (tiles32 <= 256)
     launch_score<32, 64, 2, 1>(qbar, kbar, B * H, n, nk, sm_scale, scores, block_scores, st);
   else
     launch_score<64, 16, 2, 2>(qbar, kbar, B * H, n, nk, sm_scale, scores, block_scores, st);

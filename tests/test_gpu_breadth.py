@@ -126,7 +126,7 @@ def test_full_size_f16_builder_and_attention(key):
 
 
 @pytest.mark.parametrize("kv_block", [64, 128])
-@pytest.mark.parametrize("n,H", [(1, 1), (31, 2), (32, 2), (33, 3), (65, 5), (64, 96), (64, 97), (65, 25), (97, 30), (129, 12)])
+@pytest.mark.parametrize("n,H", [(1, 1), (31, 2), (32, 2), (33, 3), (65, 5), (64, 64), (64, 65), (64, 96), (64, 97), (65, 25), (97, 30), (129, 12)])
 def test_block_scores_at_the_edges_of_their_tiles(n, H, kv_block):
     """Tiles of 32 (small launches) and of 64: sizes that end inside, at and
     past a tile and on both sides of the rule, against float64 block means and
