@@ -94,7 +94,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
 void attn_fwd_fp8_kernel(AttnArgs a, int np) {
   __shared__ __attribute__((aligned(1024))) uint8_t tiles[2][2][kTile8];   // [buffer][K, V]
   __shared__ float red[kWaves];
-  __shared__ int cnt[2][kWaves];
 
   const int item = work_item(a.order, a.B * a.H, np);
   if (item < 0) return;
@@ -136,31 +135,10 @@ void attn_fwd_fp8_kernel(AttnArgs a, int np) {
   walk.init(a, DENSE, b, h, ip);
   const bool listed_any = q_active && walk.listed(sel);
 
-  // Rotated start of each list (walk_rotation_wave's count by the whole
-  // workgroup): the pair's ids are one coalesced read of 256 lanes, where a
-  // binary search per list was a chain of dependent scalar loads ahead of the
-  // first tile.  With Q requested first and the V scales read behind the
-  // first tiles: 13 x 30 x 52 x 24 heads at 12 % (kv blocks of 128) 7 us of
-  // 565; 720p 14B, with 31 rounds of long walks, within the runs' spread.
+  // Rotated start of each list, counted from coalesced reads
   if (!DENSE) {
-    int below_a = 0, below_b = 0;
-    const int la = walk.la, lt = walk.la + walk.lb;
-    for (int t0 = 0; t0 < lt; t0 += 64 * kWaves) {
-      const int t = t0 + tid;
-      const int j = t < la ? walk.id_at(walk.a0 + t) : t < lt ? walk.id_at(walk.b0 + t - la) : INT32_MAX;
-      const bool below = j < walk.target;
-      below_a += (int)__popcll(__builtin_amdgcn_ballot_w64(below && t < la));
-      below_b += (int)__popcll(__builtin_amdgcn_ballot_w64(below && t >= la));
-    }
-    if (lane == 0) {
-      cnt[0][wave] = below_a;
-      cnt[1][wave] = below_b;
-    }
-    __syncthreads();
-    const int ra = __builtin_amdgcn_readfirstlane(cnt[0][0] + cnt[0][1] + cnt[0][2] + cnt[0][3]);
-    const int rb = __builtin_amdgcn_readfirstlane(cnt[1][0] + cnt[1][1] + cnt[1][2] + cnt[1][3]);
-    walk.ra = ra == walk.la ? 0 : ra;
-    walk.rb = rb == walk.lb ? 0 : rb;
+    walk.ra = walk_rotation_wave<KV2>(a.col_idx, walk.a0, walk.a0 + walk.la, walk.target);
+    walk.rb = walk_rotation_wave<KV2>(a.col_idx, walk.b0, walk.b0 + walk.lb, walk.target);
   }
 
   const char* kbase = static_cast<const char*>(a.k.data) + (int64_t)b * a.k.sb + (int64_t)h * a.k.sh;
