@@ -240,14 +240,17 @@ void block_mass_kernel(TensorArg q, TensorArg k, const float* __restrict__ lse, 
   flush((n - 1) / kMassGroup);
 }
 
-// Coverage of a mask: one workgroup of sixteen waves per (request, head).
-// Sixteen lanes take a row, so 64 rows are in flight, the ids are read in runs
-// of sixteen, four of a lane's ids (then their masses) at a time, and the next
-// row's bounds ahead; each lane adds its kept masses weighted by the row's
-// valid tokens in float64.  Bound by the latency of the dependent reads (id,
-// then mass) over few workgroups: 480p 14B at 15 % (40 heads x 512 rows of 77
-// ids) takes 35 us, against 164 us with one thread per row and 256 threads.
-constexpr int kCovThreads = 1024;
+// Coverage of a mask: one workgroup of sixteen waves per (request, head), of
+// four where there are no more than sixteen q-blocks.  Sixteen lanes take a row,
+// so 64 rows are in flight, the ids are read in runs of sixteen, four of a
+// lane's ids (then their masses) at a time, and the next row's bounds ahead;
+// each lane adds its kept masses weighted by the row's valid tokens in float64.
+// Bound by the latency of the dependent reads (id, then mass) over few
+// workgroups: 480p 14B at 15 % (40 heads x 512 rows of 77 ids) takes 35 us,
+// against 164 us with one thread per row and 256 threads.  Waves without a row
+// would only cost their start (1,000 units of 13 rows: 5.2 us with sixteen,
+// 3.7 with four).
+template <int kCovThreads>
 __global__ __launch_bounds__(kCovThreads) void coverage_kernel(const int32_t* __restrict__ row_ptr,
                                                                const int32_t* __restrict__ col_idx, int mask_batch,
                                                                const float* __restrict__ mass, int S, int H, int n,
@@ -310,8 +313,9 @@ hipError_t launch_block_mass(chorus_dtype dt, TensorArg q, TensorArg k, const fl
 hipError_t launch_coverage(const int32_t* row_ptr, const int32_t* col_idx, int mask_batch, const float* mass, int B,
                            int S, int H, int kvb, double* coverage, hipStream_t st) {
   const int n = blocks_of(S), nk = (S + kvb - 1) / kvb;
-  hipLaunchKernelGGL(coverage_kernel, dim3(H, B), dim3(kCovThreads), 0, st, row_ptr, col_idx, mask_batch, mass, S, H, n, nk,
-                     coverage);
+  auto kernel = n <= 16 ? coverage_kernel<256> : coverage_kernel<1024>;
+  hipLaunchKernelGGL(kernel, dim3(H, B), dim3(n <= 16 ? 256 : 1024), 0, st, row_ptr, col_idx, mask_batch, mass, S, H, n,
+                     nk, coverage);
   return hipGetLastError();
 }
 

@@ -208,9 +208,10 @@ def test_coverage_matches_oracle():
     assert (ops.mask_coverage(own, Md, S).cpu().numpy() >= 0.8 - 1e-6).all()
 
 
-@pytest.mark.parametrize("S,kv_block,p_keep", [(64 * 65 + 1, 64, 0.9), (64 * 130 - 3, 128, 0.6), (100, 64, 1.0)])
+@pytest.mark.parametrize("S,kv_block,p_keep", [(64 * 65 + 1, 64, 0.9), (64 * 130 - 3, 128, 0.6), (100, 64, 1.0),
+                                                (64 * 16, 64, 0.7), (64 * 17 - 3, 128, 0.7)])
 def test_coverage_at_the_edges_of_its_rows(S, kv_block, p_keep):
-    """64 rows at a time, 64 ids of a row at a time: more rows than one round,
+    """64 rows at a time (16 where there are no more), 64 ids of a row at a time: more rows than one round,
     rows longer than one round, empty rows, ids outside [0, n_kv) skipped; sums
     in float64 against the oracle."""
     B, H = 2, 2
