@@ -19,8 +19,9 @@ requests (B 4, H 40, S 32,760 on a 21 x 30 x 52 latent grid, bf16) sharing one
 Beside the step throughput the line carries: the attention kernel's own
 throughput and MFMA-roofline fraction (HIP events on the launch stream), the
 builder time and the routing-overhead ratio routing / (routing + attention)
-(Eq. 3), the speedup over the same kernel code at 100% density, and the CPU
-oracle's throughput on a bounded sample of the same workload.
+(Eq. 3), the speedup over the same kernel at 100% density (an explicit mask that
+lists every block), the speedup over the dense pass (no mask: a kernel of its
+own in 16 bits), and the CPU oracle's throughput on a bounded sample of the same workload.
 """
 
 from __future__ import annotations
@@ -88,6 +89,18 @@ def traffic_from_profile(kernel_file: str, workload: str, src_hash: str):
     if rec.get("source_hash") != src_hash or rec.get("kernel_file") != kernel_file:
         return None
     return rec.get("hbm_bytes_per_launch")
+
+
+def kernel_name(dtype: str, units: int, n: int, kvb: int) -> str:
+    """The instantiation that a plain masked call runs, as a kernel trace names
+    it.  16 bits: the last argument is the most parts a row's list is split
+    into, by the fullest XCD's rows (whole units to each of the 8 XCDs)."""
+    kv2 = str(kvb == 128).lower()
+    if dtype == "fp8":
+        return f"attn_fwd_fp8_kernel<false, false, {kv2}>"
+    rows = -(-units // 8) * n if units >= 8 else -(-units * n // 8)
+    parts = 1 if n < 4 or rows > 64 else 2 if rows > 32 else 4
+    return f"attn_fwd_16_kernel<{str(dtype == 'bf16').lower()}, false, false, {kv2}, {parts}>"
 
 
 def cpu_baseline(wl, inp, budget_s: float, gpu=None):
@@ -573,6 +586,13 @@ def main():
     del vmap, refreshed, ws_visit
     dense_reps = max(3, reps // 4)
     dense_ms = event_ms(lambda: attn(mask, None, dense=True), dense_reps)
+    # the same kernel at 100% density: a mask that lists every block
+    n_kv = mask.n_kv
+    full = ops.BlockMask(torch.arange(0, mask.rows * n_kv + 1, n_kv, dtype=torch.int32, device="cuda"),
+                         torch.arange(n_kv, dtype=torch.int32, device="cuda").repeat(mask.rows),
+                         mask.mask_batch, H, n, mask.block)
+    full_ms = event_ms(lambda: attn(full, sched), dense_reps)
+    del full
     attn_tflops = flops / (attn_ms * 1e-3) / 1e12
     peak = PEAK_TFLOPS[wl.dtype]
 
@@ -629,13 +649,13 @@ def main():
         "visit_update_ms": round(visit_update_ms, 4),
         "visit_refresh_worst_ms": round(visit_refresh_ms, 4),
         "routing_overhead_ratio": round(routing_ms / (routing_ms + attn_ms), 4),
+        "full_mask_attn_ms": round(full_ms, 4),
+        "speedup_vs_full_mask": round(full_ms / attn_ms, 3),
         "dense_attn_ms": round(dense_ms, 4),
         "speedup_vs_dense": round(dense_ms / attn_ms, 3),
         "ideal_speedup": round(float(mask.rows * n) / sub, 3),
         "roofline": {
-            "kernel": (f"attn_fwd_fp8_kernel<false, false, {str(kvb == 128).lower()}>" if fp8 else
-                       f"attn_fwd_16_kernel<{str(not args.f16).lower()}, false, false, "
-                       f"{str(kvb == 128).lower()}>"),
+            "kernel": kernel_name(dtype_name, B * H, n, kvb),
             "bound": "mfma",
             "achieved": round(attn_tflops, 2),
             "peak": peak,

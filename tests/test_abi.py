@@ -305,3 +305,21 @@ def test_header_is_plain_c_and_a_c_caller_links(tmp_path):
     assert r.returncode == 0, r.stderr
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("kv_block", [64, 128])
+def test_the_benchmark_names_a_kernel_that_the_library_holds(lib, kv_block):
+    """The kernel name of the benchmark's line is an instantiation of the built
+    library, so that it can be found in a kernel trace."""
+    import subprocess
+
+    import bench
+    import workloads as wk
+    names = subprocess.run(["nm", "-C", ops.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    for wl in wk.WORKLOADS.values():
+        for dtype in {wl.dtype, "f16", "bf16"} if wl.dtype != "fp8" else {"fp8"}:
+            name = bench.kernel_name(dtype, wl.B * wl.H, wl.n_blocks, kv_block)
+            assert f"::{name}(" in names, name
+    assert bench.kernel_name("f16", 2, 64, 64).endswith(", 4>")        # 16 rows per XCD
+    assert bench.kernel_name("bf16", 12, 20, 64).endswith(", 2>")      # 40 on the fullest
+    assert bench.kernel_name("bf16", 160, 512, 64).endswith(", 1>")
