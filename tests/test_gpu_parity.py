@@ -337,6 +337,54 @@ def test_attention_in_list_parts_matches_oracle(dtype, kv_block, key_scale, H, S
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("kv_block", [64, 128])
+@pytest.mark.parametrize("key_scale", [None, (200, 1.25)])
+@pytest.mark.parametrize("B,H,S,mask_batch", [(3, 30, 443, 3), (3, 30, 960, 1), (2, 40, 1025, 2), (1, 16, 2049, 1)])
+def test_unsplit_rows_at_the_edges(dtype, kv_block, key_scale, B, H, S, mask_batch):
+    """More than 64 rows on the fullest XCD, so no list is split (the kernel of
+    every large call): odd numbers of q-blocks (a missing second half with kv
+    blocks of 128), a mask per request or one for all, slices of one packed QKV
+    tensor, row maxima that rise by 2^40 along the sequence, empty rows, ids
+    outside [0, n_kv).  First, middle and last (request, head) against the
+    oracle; P rounds to the type, so the bound carries one rounding of
+    sum(p |v|)."""
+    n, nk = (S + 63) // 64, -(-S // kv_block)
+    assert -(-B * H // 8) * n > 64
+    gen = torch.Generator(device="cuda").manual_seed(S + kv_block)
+    qkv = torch.randn(B, S, 3, H, 128, generator=gen, device="cuda") * 0.5
+    qkv[:, :, 0, :, 0] = 4.0
+    qkv[:, :, 1, :, 0] += (80 * torch.arange(S, device="cuda") / S)[None, :, None]
+    qkv = qkv.to(dtype)
+    q, k, v = qkv[:, :, 0], qkv[:, :, 1], qkv[:, :, 2]
+    rng = np.random.Generator(np.random.PCG64(S))
+    rp, ci = wk.random_csr(rng, mask_batch * H * n, nk, 0.5, empty_frac=0.1)
+    rows = [ci[rp[r]:rp[r + 1]] for r in range(mask_batch * H * n)]
+    rows2 = [np.concatenate([[-1], x, [nk, nk + 5]]) if r % 4 == 3 else x for r, x in enumerate(rows)]
+    mask = ops.BlockMask.from_host(np.concatenate([[0], np.cumsum([len(x) for x in rows2])]), np.concatenate(rows2),
+                                   mask_batch, H, n, block=kv_block)
+    out, lse = ops.block_sparse_attn_fwd(q, k, v, mask, return_lse=True, key_scale=key_scale)
+    if kv_block == 128:   # bitwise the mask of 64-token blocks that lists both halves
+        half = [np.array([c for j in x for c in (2 * j, 2 * j + 1) if c < n], dtype=np.int64) for x in rows]
+        split = ops.BlockMask.from_host(np.concatenate([[0], np.cumsum([len(x) for x in half])]), np.concatenate(half),
+                                        mask_batch, H, n)
+        out2, lse2 = ops.block_sparse_attn_fwd(q, k, v, split, return_lse=True, key_scale=key_scale)
+        assert torch.equal(out.view(torch.int16), out2.view(torch.int16)) and torch.equal(lse, lse2)
+    for b, h in ((0, 0), (B - 1, H // 2), (B - 1, H - 1)):
+        qq, kk, vv = (np64(x[b:b + 1, :, h:h + 1]).astype(np.float64) for x in (q, k, v))
+        if key_scale is not None:
+            kk = og.enhance_first_frame_keys(kk, *key_scale)
+        r0 = ((b if mask_batch > 1 else 0) * H + h) * n
+        args = (rp[r0:r0 + n + 1] - rp[r0], ci[rp[r0]:rp[r0 + n]], 1.0 / math.sqrt(128), 1)
+        O, L = oa.attention(qq, kk, vv, *args, kv_block=kv_block)
+        A, _ = oa.attention(qq, kk, np.abs(vv), *args, kv_block=kv_block)
+        assert within_rounding(np64(out[b:b + 1, :, h:h + 1]), O, dtype, ref_abs=A)
+        got = lse[b:b + 1, h:h + 1].cpu().numpy()
+        fin = np.isfinite(L)
+        assert np.array_equal(np.isfinite(got), fin)
+        assert np.max(np.abs(got[fin] - L[fin])) <= 1e-3
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 @pytest.mark.parametrize("B,S,H", [(1, 189, 600), (1, 250, 200), (2, 850, 20), (1, 1950, 40), (1, 4150, 8), (2, 4150, 32)])
 def test_dense_over_growing_logits_matches_oracle(dtype, B, S, H):
     """No mask, with rows not split: the masked kernel's workgroups (3, 4 and 14
