@@ -318,8 +318,9 @@ chorus_status chorus_quantize_fp8_blockwise_sums(chorus_dtype in_dtype, const ch
  *   accumulation; P is rounded to e4m3 for PV.  out is bf16.
  * mask     : the block mask; NULL means every q-block attends to every
  *            kv-block (dense attention -- the paper's fallback when no cached
- *            mask is available, Sec. 3.2 "Mask Caching and Retrieval"; also
- *            the 100%-density reference of the same kernel code).
+ *            mask is available, Sec. 3.2 "Mask Caching and Retrieval").  In
+ *            16 bits larger dense calls run a kernel of their own; a mask that
+ *            lists every block runs the masked kernel at 100% density.
  * lse      : optional out (NULL to skip), device float32 [B, H, S] contiguous.
  * schedule : optional work order from chorus_plan_block_mask (NULL = the
  *            library's default order); never changes results.
@@ -327,7 +328,13 @@ chorus_status chorus_quantize_fp8_blockwise_sums(chorus_dtype in_dtype, const ch
  *            logits of keys c < n_first are multiplied by beta, as if K had
  *            been scaled by Eq. (1) (for fp8: the dequantised keys).
  * workspace: device scratch of chorus_attn_workspace_size() bytes (may be 0).
- * Results are bitwise deterministic for a given input, mask and dtype.
+ * Results are bitwise deterministic for a given shape, input, mask and dtype,
+ * with any schedule.  In f16 / bf16 the rounding of a row may depend on how
+ * many (request, head) units share the launch: with up to 64 q-blocks on the
+ * XCD that holds most (units / 8, rounded up, times n_blocks; with fewer than
+ * 8 units units * n_blocks / 8) a row's kv list is accumulated in two or four parts, so a request attended alone and within
+ * a batch can differ by rounding (about 4e-4 relative in f16, 3e-3 in bf16;
+ * the error against exact arithmetic is the same).
  * ------------------------------------------------------------------------- */
 size_t chorus_attn_workspace_size(chorus_dtype dtype, const chorus_shape* shape,
                                   const chorus_block_mask* mask);

@@ -385,6 +385,28 @@ def test_unsplit_rows_at_the_edges(dtype, kv_block, key_scale, B, H, S, mask_bat
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("H,n", [(40, 14), (40, 8), (8, 40)])
+def test_a_request_alone_and_in_a_batch(dtype, H, n):
+    """As the header says: a launch that splits no list gives a request the same
+    bits alone and in a batch of three (40 heads x 14 blocks, 70 and 210 rows on
+    the fullest XCD); where the launch alone splits them (40 and 40 rows) the two
+    differ by rounding only."""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    q, k, v = (torch.randn(3, 64 * n, H, 128, generator=gen, device="cuda").to(dtype) for _ in range(3))
+    rp, ci = wk.random_csr(np.random.Generator(np.random.PCG64(n)), H * n, n, 0.6)
+    mask = ops.BlockMask.from_host(rp, ci, 1, H, n)
+    batch = ops.block_sparse_attn_fwd(q, k, v, mask)
+    alone = ops.block_sparse_attn_fwd(q[1:2], k[1:2], v[1:2], mask)
+    if H // 8 * n > 64:
+        assert torch.equal(batch[1:2].view(torch.int16), alone.view(torch.int16))
+    else:
+        # both round P and O once: within two roundings of sum(p |v|) and of O
+        bound = ops.block_sparse_attn_fwd(q, k, v.abs(), mask)[1:2].float() + batch[1:2].float().abs()
+        rel = 2.0 ** (-8 if dtype == torch.bfloat16 else -11)
+        assert bool(((batch[1:2].float() - alone.float()).abs() <= 2 * rel * bound).all())
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 @pytest.mark.parametrize("B,S,H", [(1, 189, 600), (1, 250, 200), (2, 850, 20), (1, 1950, 40), (1, 4150, 8), (2, 4150, 32)])
 def test_dense_over_growing_logits_matches_oracle(dtype, B, S, H):
     """No mask, with rows not split: the masked kernel's workgroups (3, 4 and 14
