@@ -29,9 +29,9 @@
 // What bounds it: the tile feed (L2 misses, and the clock under that load)
 // and the vector instructions beside the MFMAs.  Same bits as the version that
 // ran QK^T, softmax and PV of a 64-key block one after the other on single
-// buffers, and faster: batch-4 480p 14B (bf16, 15 %) 14.09 against 15.00 ms,
-// 720p 5B (bf16, 20 %) 2.00 against 2.10 ms, f16 with kv blocks of 128 and a
-// key scale (2 x 16 heads, S = 17,523) 1.20 against 1.26 ms.  Measured beside
+// buffers, and faster: batch-4 480p 14B (bf16, 15 %) 13.93 against 14.76 ms,
+// 720p 5B (bf16, 20 %) 1.99 against 2.09 ms, f16 with kv blocks of 128 and a
+// key scale (2 x 16 heads, S = 17,523) 1.16 against 1.21 ms.  Measured beside
 // it: two q-blocks per workgroup walking the union of their lists 15.8 ms
 // (every fifth step has work for one of them only), separate waits for K and V
 // 15.60 against 15.17 ms, raised wave priority during QK^T 15.39.
@@ -517,7 +517,7 @@ struct SharedTileLoader {
 // the natural order of the kv blocks: an explicit full mask gives the same bits
 // up to 14 kv blocks, beyond which some rows' masked walks start rotated.
 // Measured at 480p 14B (S = 32,760, 40 heads, bf16): 17.8-18.6 ms, 1,180-1,230
-// TFLOP/s, matrix cores busy 64 % of the cycles, against 22.8-23.2 ms for the
+// TFLOP/s, matrix cores busy 62 % of the cycles, against 22.8-23.2 ms for the
 // masked kernel's two-wave workgroup (46 %); four waves 19.0 ms.  What is left
 // is the clock (1.8 GHz under this load) and the issue of the softmax's vector
 // instructions.

@@ -19,9 +19,10 @@
 // global -> LDS loads, one barrier per kv block.  The per-lane sums of four
 // kv blocks are reduced over the wave together (ten instructions instead of
 // four times six LDS-crossbar steps) and sixteen blocks' masses are written
-// together (64-byte runs).  480p 14B (S = 32,760, 40 heads), bf16: 9.8 ms,
-// 1,125 TFLOP/s of QK^T, against 18.9 ms for the earlier workgroup of one
-// q-block (two waves, a shuffle reduction and a four-byte store per kv block).
+// together (64-byte runs).  480p 14B (S = 32,760, 40 heads), bf16: 9.8-10.2 ms,
+// 1,080-1,125 TFLOP/s of QK^T, matrix cores busy 57 % of the cycles, against
+// 18.9 ms for the earlier workgroup of one q-block (two waves, a shuffle
+// reduction and a four-byte store per kv block).
 // Four waves of the same code: 10.0 ms; three waves per SIMD 10.3 ms; QK^T of
 // the next block issued beside this block's exponentials (a second score
 // tile, two waves per SIMD) 10.8 ms.
